@@ -27,7 +27,6 @@ constexpr int kAGroup = 8;        // owners per READ block: W0 is read once for 
 constexpr int kAURows = kAChunk / 64;   // chunk rows per lane in the u share
 constexpr int kARedCols = 64;     // READ reduce: columns per block (four waves split the chunks)
 constexpr int kARedLoads = 16;    // READ reduce: partials in flight per lane
-constexpr int kAPQRows = 64;      // evidence rows of P or Q staged per pass of the update
 
 __device__ __forceinline__ float to_f32(float v) { return v; }
 __device__ __forceinline__ float to_f32(uint16_t v) { return __uint_as_float(uint32_t(v) << 16); }
@@ -390,20 +389,44 @@ __global__ void __launch_bounds__(256) adapter_read_reduce_kernel(const AReadPar
 // WRITE
 // ---------------------------------------------------------------------------
 //
-// 1. adapter_pq_kernel: one block per (evidence row c, slice of 1024 columns
-//    of G / rows of Z) forms that slice's share of P[c][j] = sum_n G[c][n] B[j][n]
-//    or Q[c][j] = sum_k Z[c][k] A[k][j] (four elements per thread in order, a
-//    butterfly in each wave, then the four waves in order).
-// 2. adapter_update_kernel: one block per 64 rows k of A or columns n of B;
-//    its four waves take a quarter of the evidence rows each:
-//    A'[k][j] = A[k][j] + eta sum_c Z[c][k] P[c][j] and
-//    B'[j][n] = B[j][n] + eta sum_c Q[c][j] G[c][n], each quarter's sum in c
-//    order, the quarters added in order; P and Q (their slices added in
-//    order) are staged in LDS; the result is written to the shadow slot in
-//    the state dtype.
+// Both steps are contractions against the fp32 factors and run on the fp32
+// matrix instruction v_mfma_f32_16x16x4_f32 (fp32 products, fp32 sums: nothing
+// is narrowed).  Their traffic is the evidence, read once by each kernel, and a
+// few passes of L2 over the factors and their products with the evidence.  Four
+// owners at 9728 x 2560, rank 16, C = 256 (31 MB): 12.9 + 12.7 us, down from 75.2
+// + 36.5 us when a block took one evidence row (and read the whole factor slice
+// for it) and one thread one value; three owners at 4608 x 304, rank 26, C = 735:
+// 37 against 422 us.  What is left is the latency of dependent loads (few
+// waves, two launches) and, for large C r, the matrix rate.
+//
+// 1. adapter_pq_kernel: one 512-thread block per (tile of 16 CT evidence rows
+//    c, slice of 1024 columns of G / rows of Z, owner) forms the slice's share of
+//    P[c][j] = sum_n G[c][n] B[j][n] or Q[c][j] = sum_k Z[c][k] A[k][j].  Each of
+//    the eight waves contracts 128 elements for all 16 CT rows and all rank
+//    columns (JT tiles of 16); a lane's 16 bytes of evidence feed eight (bf16)
+//    matrix steps.  The waves' sums are added as a tree.  The factor slice is
+//    read once per evidence tile: CT = 4 halves that L2 traffic where rank <= 16
+//    leaves the registers for it and C > 128 the blocks.
+// 2. adapter_update_kernel: one block of NW waves per 64 rows k of A or columns
+//    n of B, all rank columns: A'[k][j] = A[k][j] + eta sum_c Z[c][k] P[c][j] and
+//    B'[j][n] = B[j][n] + eta sum_c Q[c][j] G[c][n].  The waves take contiguous
+//    shares of the evidence rows, each sum in c order (four rows per matrix
+//    step), then the waves as a tree; the slice shares of P and Q are added in
+//    slice order in the register that feeds the matrix step, so the kernel has
+//    no staging and no barrier before its last sum.
+//
+// Every order depends only on the shapes and the chunk.
 
 constexpr int kASlice = 1024;    // columns of G / rows of Z per P / Q block
-constexpr int kAUpdCols = 64;    // A rows or B columns per update block
+constexpr int kAUpdRows = 64;    // A rows or B columns per update block
+constexpr int kAWWaves = 8;      // waves of a WRITE block
+constexpr int kAWThreads = 64 * kAWWaves;
+
+// Sum of N (a power of two) waves' values as a balanced tree.
+template <int N, typename F> __device__ __forceinline__ float wave_sum(F v, int first = 0) {
+  if constexpr (N == 1) return v(first);
+  else return wave_sum<N / 2>(v, first) + wave_sum<N / 2>(v, first + N / 2);
+}
 
 struct AWriteParams {
   int count, chunk, d_ff, d_model, rank, max_chunk, sp, sq;   // sp, sq: slices of N, K
@@ -417,197 +440,240 @@ struct AWriteParams {
   uint32_t row[RWTTT_MAX_GROUP];
 };
 
-template <typename IO, typename ST>
-__global__ void __launch_bounds__(256) adapter_pq_kernel(const AWriteParams p) {
-  constexpr int EPT = kASlice / 256;       // evidence elements per thread
-  constexpr int kQLoads = 32;              // A requests in flight per thread (Q, power-of-two rank)
-  __shared__ float wsum[4][RWTTT_MAX_RANK];
-  __shared__ float zs[kASlice];
+// Element at a 32-bit byte offset from a wave-uniform base: one scalar base and
+// one vector register of address instead of 64-bit arithmetic in every lane.
+template <typename T> __device__ __forceinline__ const T* at_byte(const void* base, uint32_t off) {
+  return reinterpret_cast<const T*>(static_cast<const char*>(base) + off);
+}
+
+template <typename IO, typename ST, int JT, int CT>
+__global__ void __launch_bounds__(kAWThreads) adapter_pq_kernel(const AWriteParams p) {
+  constexpr int KW = kASlice / kAWWaves;   // contracted elements per wave
+  constexpr int KG = 32;                   // elements per group of loads: 4 quarter-waves x 8
+  constexpr int NG = KW / KG;
+  __shared__ float red[kAWWaves][16 * CT][16 * JT + 1];
   const int b = blockIdx.z;
-  const int c = blockIdx.y;
   const int s = blockIdx.x;                // < sp: a P slice; else a Q slice
+  const int c0 = int(blockIdx.y) * 16 * CT;
   const bool is_p = s < p.sp;
-  const int i0 = (is_p ? s : s - p.sp) * kASlice;
   const int lim = is_p ? p.d_model : p.d_ff;
   const ST* A = static_cast<const ST*>(p.live[b]);
   const ST* F = is_p ? A + size_t(p.d_ff) * p.rank : A;   // B for P, A for Q
-  const IO* E = static_cast<const IO*>(is_p ? p.g[b] : p.z[b]) + size_t(c) * lim;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  float* out = (is_p ? p.P + ((size_t(p.row[b]) * p.max_chunk + c) * p.sp + s) * p.rank
-                     : p.Q + ((size_t(p.row[b]) * p.max_chunk + c) * p.sq + (s - p.sp)) * p.rank);
-  // requests first, unconditional (indices clamped, unused values dropped):
-  // the evidence elements, then each rank pass's factor values
-  float ev[EPT];
+  const IO* E = static_cast<const IO*>(is_p ? p.g[b] : p.z[b]) + size_t(c0) * lim;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i16 = lane & 15, kq = lane >> 4;
+  const int i0 = (is_p ? s : s - p.sp) * kASlice + wave * KW;
+
+  // lane (i16, kq) holds elements kb .. kb+7 of evidence row c0 + i16 (+ 16 ci)
+  // and of factor column i16 (+ 16 jt); matrix step t contracts the four
+  // quarters' element t.  Addresses past the matrix are clamped into it and
+  // both operands zeroed (eight elements are in or out together: the extents
+  // are multiples of 8); rows past the chunk and columns past the rank only
+  // reach sums that are not stored.
+  uint32_t eoff[CT], foff[JT];             // byte offsets of element 0 of row / column i16
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) ev[e] = Elem<IO>::get(E, min(i0 + e * 256 + tid, lim - 1));
-  const int r = p.rank;
-  if (!is_p && (r & (r - 1)) == 0) {
-    // Q with a power-of-two rank: the slice's A rows are one contiguous run of
-    // 1024 r floats; thread t reads flat elements t, t + 256, ... (consecutive
-    // lanes on consecutive addresses), all of rank column t mod r, against
-    // the Z values of their rows staged in LDS.  Per thread in flat order,
-    // then a butterfly over the lanes of one column, then the waves in order.
+  for (int ci = 0; ci < CT; ++ci)
+    eoff[ci] = uint32_t(min(16 * ci + i16, p.chunk - 1 - c0)) * uint32_t(lim) * uint32_t(sizeof(IO));
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) zs[e * 256 + tid] = i0 + e * 256 + tid < lim ? ev[e] : 0.f;
-    lds_barrier();
-    const int lr = __builtin_ctz(r);
-    const size_t base = size_t(i0) * r, last = size_t(p.d_ff) * r - 1;
-    float acc = 0.f;
-    for (int m0 = 0; m0 < 4 * r; m0 += kQLoads) {
-      float a[kQLoads];
+  for (int jt = 0; jt < JT; ++jt)
+    foff[jt] = uint32_t(min(16 * jt + i16, p.rank - 1)) * uint32_t(is_p ? p.d_model : 1) * uint32_t(sizeof(ST));
+
+  f32x4_t acc[CT][JT];
 #pragma unroll
-      for (int q = 0; q < kQLoads; ++q)
-        a[q] = Elem<ST>::get(A, min(base + size_t(tid + 256 * min(m0 + q, 4 * r - 1)), last));
+  for (int ci = 0; ci < CT; ++ci)
 #pragma unroll
-      for (int q = 0; q < kQLoads; ++q)
-        if (m0 + q < 4 * r) acc = fmaf(zs[(tid + 256 * (m0 + q)) >> lr], a[q], acc);
-    }
-    for (int m = 32; m >= r; m >>= 1) acc += __shfl_xor(acc, m);
-    if (lane < r) wsum[wave][lane] = acc;
-    lds_barrier();
-    if (tid < r) out[tid] = ((wsum[0][tid] + wsum[1][tid]) + wsum[2][tid]) + wsum[3][tid];
-    return;
-  }
-  for (int j0 = 0; j0 < p.rank; j0 += 8) {
-    float f[EPT][8];
+    for (int jt = 0; jt < JT; ++jt) acc[ci][jt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  auto contract = [&](auto isp) {
+    constexpr bool IS_P = decltype(isp)::value;
+    struct Ops { Packed<IO, 8> e[CT]; Packed<ST, 8> v[IS_P ? JT : 1]; ST f[IS_P ? 1 : JT][8]; };
+    auto load = [&](Ops& o, int g) {
+      const uint32_t kc = uint32_t(min(i0 + g * KG + 8 * kq, lim - 8));
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const int ic = min(i0 + e * 256 + tid, lim - 1);
+      for (int ci = 0; ci < CT; ++ci)
+        load_packed<false>(at_byte<IO>(E, eoff[ci] + kc * uint32_t(sizeof(IO))), o.e[ci]);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int jj = min(j0 + j, p.rank - 1);
-        f[e][j] = Elem<ST>::get(F, is_p ? size_t(jj) * p.d_model + ic : size_t(ic) * p.rank + jj);
+      for (int jt = 0; jt < JT; ++jt) {
+        if constexpr (IS_P) {
+          load_packed<false>(at_byte<ST>(F, foff[jt] + kc * uint32_t(sizeof(ST))), o.v[jt]);
+        } else {
+          const uint32_t step = uint32_t(p.rank) * uint32_t(sizeof(ST));
+          const char* Ft = reinterpret_cast<const char*>(F);
+#pragma unroll
+          for (int t = 0; t < 8; ++t) o.f[jt][t] = *at_byte<ST>(Ft + t * step, foff[jt] + kc * step);
+        }
       }
+    };
+    auto mul = [&](const Ops& o, int g) {
+      const bool ok = i0 + g * KG + 8 * kq < lim;
+      // four short chains from zero (8 products each), added as a tree to the
+      // running sum: one chain over the wave's 128 products rounds more often
+      // (2.3e-7 against 1.4e-7 from 64 bits at C = 256, 9728 x 2560)
+#pragma unroll
+      for (int ci = 0; ci < CT; ++ci)
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt) {
+          f32x4_t h[4];
+#pragma unroll
+          for (int t = 0; t < 8; ++t) {
+            float fv;
+            if constexpr (IS_P) fv = o.v[jt].get(t);
+            else fv = to_f32(o.f[jt][t]);
+            h[t >> 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                ok ? o.e[ci].get(t) : 0.f, ok ? fv : 0.f, (t & 1) ? h[t >> 1] : f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+          }
+          acc[ci][jt] += (h[0] + h[1]) + (h[2] + h[3]);
+        }
+    };
+    // two sets of operands: a group's loads are in flight while the one before
+    // it is multiplied
+    Ops o[2];
+    load(o[0], 0);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      if (g + 1 < NG) load(o[(g + 1) & 1], g + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(o[g & 1], g);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    float acc[8];
+  };
+  if (is_p) contract(std::true_type{});
+  else contract(std::false_type{});
+  // register q of lane (i16, kq) holds row 4 kq + q, column i16 of a 16 x 16 tile
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+  for (int ci = 0; ci < CT; ++ci)
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const float x = i0 + e * 256 + tid < lim ? ev[e] : 0.f;
+    for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) acc[j] = fmaf(x, f[e][j], acc[j]);
-    }
-    // the block's sum: a butterfly in each wave, then the four waves in order
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[j] += __shfl_xor(acc[j], m);
-    if (lane == 0) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) wsum[wave][j] = acc[j];
-    }
-    lds_barrier();
-    if (tid < 8 && j0 + tid < p.rank)
-      out[j0 + tid] = ((wsum[0][tid] + wsum[1][tid]) + wsum[2][tid]) + wsum[3][tid];
-    lds_barrier();
+      for (int q = 0; q < 4; ++q) red[wave][16 * ci + 4 * kq + q][16 * jt + i16] = acc[ci][jt][q];
+  lds_barrier();
+  const int ns = is_p ? p.sp : p.sq, sl = is_p ? s : s - p.sp;
+  float* out = (is_p ? p.P : p.Q) + (size_t(p.row[b]) * p.max_chunk + c0) * ns * p.rank;
+  const int items = min(16 * CT, p.chunk - c0) * p.rank;
+  for (int t = tid; t < items; t += kAWThreads) {
+    const int c = t / p.rank, j = t - c * p.rank;
+    out[(size_t(c) * ns + sl) * p.rank + j] = wave_sum<kAWWaves>([&](int w) { return red[w][c][j]; });
   }
 }
 
-template <typename IO, typename ST>
-__global__ void __launch_bounds__(256) adapter_update_kernel(const AWriteParams p) {
-  constexpr int RPW = kAPQRows / 4;        // evidence rows per wave and pass
-  constexpr int kPQItems = 2;              // P / Q items per thread whose shares are requested early
-  __shared__ float pq[kAPQRows * RWTTT_MAX_RANK];
-  __shared__ float part[4][kAUpdCols][RWTTT_MAX_RANK + 1];
+template <typename IO, typename ST, int JT, int NW>
+__global__ void __launch_bounds__(64 * NW) adapter_update_kernel(const AWriteParams p) {
+  constexpr int QB = 4;                    // matrix steps (of four evidence rows) per group of loads
+  constexpr int SB = 3;                    // further slice shares of P or Q in flight
+  constexpr int NL = kAUpdRows * 16 * JT / (64 * NW);   // most values a thread finishes
+  __shared__ float red[NW][16 * JT][kAUpdRows + 1];
   const int b = blockIdx.y;
-  const int na = (p.d_ff + kAUpdCols - 1) / kAUpdCols;
+  const int na = (p.d_ff + kAUpdRows - 1) / kAUpdRows;
   const bool is_a = int(blockIdx.x) < na;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int i = (is_a ? int(blockIdx.x) : int(blockIdx.x) - na) * kAUpdCols + lane;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i16 = lane & 15, cq = lane >> 4;
+  const int i0 = (is_a ? int(blockIdx.x) : int(blockIdx.x) - na) * kAUpdRows;
   const int lim = is_a ? p.d_ff : p.d_model;
-  const int ic = min(i, lim - 1);
+  const int rows = min(kAUpdRows, lim - i0);
   const int ns = is_a ? p.sp : p.sq;        // A uses P (slices of N); B uses Q (slices of K)
-  const float* src = (is_a ? p.P : p.Q) + size_t(p.row[b]) * p.max_chunk * ns * p.rank;
+  const float* S = (is_a ? p.P : p.Q) + size_t(p.row[b]) * p.max_chunk * ns * p.rank;
   const IO* E = static_cast<const IO*>(is_a ? p.z[b] : p.g[b]);
-  const int ld = is_a ? p.d_ff : p.d_model;
-  const ST* live = static_cast<const ST*>(p.live[b]);
-  ST* shadow = static_cast<ST*>(p.shadow[b]);
-  auto at_of = [&](int j) {
-    return is_a ? size_t(ic) * p.rank + j : size_t(p.d_ff) * p.rank + size_t(j) * p.d_model + ic;
+  const ST* live = static_cast<const ST*>(p.live[b]) +
+                   (is_a ? size_t(i0) * p.rank : size_t(p.d_ff) * p.rank + i0);
+  ST* shadow = static_cast<ST*>(p.shadow[b]) + (live - static_cast<const ST*>(p.live[b]));
+  // value t of the block: A row i0 + t / r, column t % r (one contiguous run),
+  // or B row t / 64, column i0 + t % 64
+  const int nv = is_a ? rows * p.rank : kAUpdRows * p.rank;
+  auto at_of = [&](int t) {
+    return is_a ? uint32_t(t) : uint32_t(t / kAUpdRows) * uint32_t(p.d_model) + uint32_t(min(t % kAUpdRows, rows - 1));
   };
-  // the live values of the first two rank columns this thread finishes
-  // (j = wave, wave + 4), requested first
-  float lv[2];
+  float lv[NL];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) lv[h] = Elem<ST>::get(live, at_of(min(wave + 4 * h, p.rank - 1)));
-  float acc[RWTTT_MAX_RANK];
+  for (int h = 0; h < NL; ++h)
+    lv[h] = to_f32(*at_byte<ST>(live, at_of(min(tid + (64 * NW) * h, nv - 1)) * uint32_t(sizeof(ST))));
+
+  f32x4_t acc[4][JT];
 #pragma unroll
-  for (int j = 0; j < RWTTT_MAX_RANK; ++j) acc[j] = 0.f;
-  for (int c0 = 0; c0 < p.chunk; c0 += kAPQRows) {
-    const int cn = min(kAPQRows, p.chunk - c0);
-    // this wave's quarter of the pass's rows, in c order
-    const int q0 = (cn * wave) / 4, q1 = (cn * (wave + 1)) / 4;
-    float ev[RPW];
+  for (int t = 0; t < 4; ++t)
 #pragma unroll
-    for (int r = 0; r < RPW; ++r) ev[r] = Elem<IO>::get(E, size_t(c0 + min(q0 + r, cn - 1)) * ld + ic);
-    // P / Q rows c0 .. c0+cn: their slice shares added in slice order.  The
-    // first kPQItems items of each thread have their first NS shares
-    // requested at once, before the barrier that frees pq (NS: the slice
-    // count rounded up to 4, 8 or 16); further shares are loaded after it.
-    const int items = cn * p.rank;
-    auto stage = [&](auto nsl) {
-      constexpr int NS = decltype(nsl)::value;
-      float sh[kPQItems][NS];
+    for (int jt = 0; jt < JT; ++jt) acc[t][jt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  // lane (i16, cq) holds evidence row 4 q + cq at columns i0 + 4 i16 .. + 3: row
+  // i16 of matrix t is column i0 + 4 i16 + t.  Rows past the chunk are clamped
+  // and both operands zeroed.
+  const uint32_t ec = uint32_t(min(i0 + 4 * i16, lim - 4)) * uint32_t(sizeof(IO));
+  // matrix column i16 of tile jt is rank column JT i16 + jt
+  const uint32_t jc = uint32_t(min(JT * i16, p.rank - JT)) * 4u;
+  const bool odd = JT * i16 == p.rank - 1;
+  const uint32_t spitch = uint32_t(ns) * uint32_t(p.rank) * 4u;
+  const int nq = (p.chunk + 3) / 4, per = (nq + NW - 1) / NW;
+  const int q1 = min(nq, (wave + 1) * per);
+  auto share = [&](const char* Sk, uint32_t off, float (&f)[JT]) {
+    if constexpr (JT == 1) {
+      f[0] = *at_byte<float>(Sk, off);
+    } else {
+      // columns 2 i16 and 2 i16 + 1 in one load (4-byte aligned); an odd rank's
+      // last lane steps back one column and takes the upper half
+      struct __attribute__((packed, aligned(4))) Two { float v[2]; };
+      const Two w = *at_byte<Two>(Sk, off);
+      f[0] = odd ? w.v[1] : w.v[0];
+      f[1] = w.v[1];
+    }
+  };
+  for (int q0 = wave * per; q0 < q1; q0 += QB) {
+    Packed<IO, 4> e[QB];
+    float f[QB][JT];
+    const IO* Eq = E + size_t(4 * q0) * lim;
+    const char* Sq = reinterpret_cast<const char*>(S) + size_t(4 * q0) * spitch;
+    uint32_t so[QB];
 #pragma unroll
-      for (int it = 0; it < kPQItems; ++it) {
-        const int t = min(int(threadIdx.x) + 256 * it, items - 1);
-        const int cc = t / p.rank, j = t - cc * p.rank;
-        const float* q = src + (size_t(c0 + cc) * ns) * p.rank + j;
+    for (int u = 0; u < QB; ++u) {
+      const uint32_t c = uint32_t(min(4 * u + cq, p.chunk - 1 - 4 * q0));
+      load_packed<false>(at_byte<IO>(Eq, c * uint32_t(lim) * uint32_t(sizeof(IO)) + ec), e[u]);
+      so[u] = c * spitch + jc;
+      share(Sq, so[u], f[u]);
+    }
+    for (int sl = 1; sl < ns; sl += SB) {
+      float a[SB][QB][JT];
 #pragma unroll
-        for (int sl = 0; sl < NS; ++sl) sh[it][sl] = q[size_t(min(sl, ns - 1)) * p.rank];
+      for (int k = 0; k < SB; ++k) {
+        const char* Sk = Sq + size_t(min(sl + k, ns - 1)) * p.rank * 4;
+#pragma unroll
+        for (int u = 0; u < QB; ++u) share(Sk, so[u], a[k][u]);
       }
-      lds_barrier();   // the previous pass's P / Q rows are no longer read
-      for (int t = threadIdx.x, it = 0; t < items; t += 256, ++it) {
-        const int cc = t / p.rank, j = t - cc * p.rank;
-        const float* q = src + (size_t(c0 + cc) * ns) * p.rank + j;
-        float v = 0.f;
-        if (it < kPQItems) {
 #pragma unroll
-          for (int sl = 0; sl < NS; ++sl) v += sl < ns ? (it == 0 ? sh[0][sl] : sh[kPQItems - 1][sl]) : 0.f;
+      for (int k = 0; k < SB; ++k)
+#pragma unroll
+        for (int u = 0; u < QB; ++u)
+#pragma unroll
+          for (int jt = 0; jt < JT; ++jt) f[u][jt] = sl + k < ns ? f[u][jt] + a[k][u][jt] : f[u][jt];
+    }
+    // one short chain from zero per group (16 products), added to the running sum
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) {
+        f32x4_t h = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < QB; ++u) {
+          const bool ok = q0 + u < q1 && 4 * (q0 + u) + cq < p.chunk;
+          h = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? e[u].get(t) : 0.f, ok ? f[u][jt] : 0.f, h, 0, 0, 0);
         }
-        for (int sl0 = it < kPQItems ? NS : 0; sl0 < ns; sl0 += 8) {
-          float a2[8];
-#pragma unroll
-          for (int k = 0; k < 8; ++k) a2[k] = q[size_t(min(sl0 + k, ns - 1)) * p.rank];
-#pragma unroll
-          for (int k = 0; k < 8; ++k) v += sl0 + k < ns ? a2[k] : 0.f;
-        }
-        pq[t] = v;
+        acc[t][jt] += h;
       }
-    };
-    if (ns <= 4) stage(std::integral_constant<int, 4>{});
-    else if (ns <= 8) stage(std::integral_constant<int, 8>{});
-    else stage(std::integral_constant<int, 16>{});
-    lds_barrier();
-    // this wave's rows in c order; the rank loop is branch-free (columns past
-    // the rank read a valid pq entry and are never stored)
-    auto rows = [&](auto rk) {
-      constexpr int R = decltype(rk)::value;
-#pragma unroll
-      for (int r = 0; r < RPW; ++r) {
-        if (q0 + r < q1) {
-          const float* row = pq + (q0 + r) * p.rank;
-#pragma unroll
-          for (int j = 0; j < R; ++j) acc[j] = fmaf(ev[r], row[min(j, p.rank - 1)], acc[j]);
-        }
-      }
-    };
-    if (p.rank <= 8) rows(std::integral_constant<int, 8>{});
-    else if (p.rank <= 16) rows(std::integral_constant<int, 16>{});
-    else rows(std::integral_constant<int, RWTTT_MAX_RANK>{});
   }
-  // the four quarters in wave order
 #pragma unroll
-  for (int j = 0; j < RWTTT_MAX_RANK; ++j)
-    if (j < p.rank) part[wave][lane][j] = acc[j];
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) red[wave][JT * i16 + jt][4 * (4 * cq + q) + t] = acc[t][jt][q];
   lds_barrier();
-  if (i >= lim) return;
   const float eta = p.eta;
-  for (int j = wave, h = 0; j < p.rank; j += 4, ++h) {
-    const float d = ((part[0][lane][j] + part[1][lane][j]) + part[2][lane][j]) + part[3][lane][j];
-    const float l = h == 0 ? lv[0] : h == 1 ? lv[1] : Elem<ST>::get(live, at_of(j));
-    Elem<ST>::put(shadow, at_of(j), l + eta * d);
+#pragma unroll
+  for (int h = 0; h < NL; ++h) {
+    const int t = tid + (64 * NW) * h;
+    const int k = is_a ? t / p.rank : t % kAUpdRows, j = is_a ? t - k * p.rank : t / kAUpdRows;
+    if (t < nv && k < rows) {
+      const float d = wave_sum<NW>([&](int w) { return red[w][j][k]; });
+      Elem<ST>::put(shadow, at_of(t), lv[h] + eta * d);
+    }
   }
 }
 
@@ -665,11 +731,33 @@ hipError_t launch_adapter_write_t(const AdapterWriteLaunch& L, hipStream_t strea
     p.g[b] = in ? L.g[b] : nullptr;
     p.row[b] = in ? L.row[b] : 0u;
   }
-  hipLaunchKernelGGL((adapter_pq_kernel<IO, ST>), dim3(p.sp + p.sq, L.chunk, L.count), dim3(256),
-                     0, stream, p);
-  const unsigned blocks = unsigned((L.d_ff + kAUpdCols - 1) / kAUpdCols +
-                                   (L.d_model + kAUpdCols - 1) / kAUpdCols);
-  hipLaunchKernelGGL((adapter_update_kernel<IO, ST>), dim3(blocks, L.count), dim3(256), 0, stream, p);
+  const unsigned slices = unsigned(p.sp + p.sq), owners = unsigned(L.count);
+  const unsigned tiles = unsigned((L.d_ff + kAUpdRows - 1) / kAUpdRows + (L.d_model + kAUpdRows - 1) / kAUpdRows);
+  auto pq = [&](auto jt, auto ct) {
+    constexpr int JT = decltype(jt)::value, CT = decltype(ct)::value;
+    hipLaunchKernelGGL((adapter_pq_kernel<IO, ST, JT, CT>),
+                       dim3(slices, unsigned((L.chunk + 16 * CT - 1) / (16 * CT)), owners), dim3(kAWThreads), 0,
+                       stream, p);
+  };
+  auto update = [&](auto jt, auto nw) {
+    constexpr int JT = decltype(jt)::value, NW = decltype(nw)::value;
+    hipLaunchKernelGGL((adapter_update_kernel<IO, ST, JT, NW>), dim3(tiles, owners), dim3(64 * NW), 0, stream, p);
+  };
+  using one = std::integral_constant<int, 1>;
+  using two = std::integral_constant<int, 2>;
+  using four = std::integral_constant<int, 4>;
+  using eight = std::integral_constant<int, 8>;
+  if (L.rank > 16) pq(two{}, two{});
+  else if (L.chunk <= 128) pq(one{}, two{});
+  else pq(one{}, four{});
+  auto by_waves = [&](auto jt) {
+    // a wave's group of loads is 16 evidence rows: eight waves have work for
+    // each only above 64 (4.9 against 5.6 us at C = 64, one owner, rank 8)
+    if (L.chunk <= 64) update(jt, four{});
+    else update(jt, eight{});
+  };
+  if (L.rank > 16) by_waves(two{});
+  else by_waves(one{});
   return hipGetLastError();
 }
 
