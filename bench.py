@@ -209,7 +209,7 @@ def write_kernel_name(wl, chunk, rank=0):
     if rank:
         return "adapter_pq_kernel+adapter_update_kernel"
     if wl.io_dtype != "bf16":
-        return "write_valu_kernel"
+        return "write_f32_kernel"
     return "write_stream_kernel" if chunk <= 64 else "write_gemm_kernel"
 
 

@@ -262,10 +262,10 @@ rwttt_status rwttt_read_append(rwttt_ctx* ctx, const rwttt_group* group, const u
  * maps (r, x_r, u_r, s_r^v) to (y_r, s_r^{v+1})): with x and y non-null
  * (owner-indexed as in rwttt_read) it also computes
  *     y[r, :] = x[r, :] W0_layer + x[r, :] live_{r,layer}
- * at version v, the candidate being invisible until commit.  For bf16
- * evidence and chunk <= 64 the token is fused into the update kernel, which
- * reads the live state once for both; otherwise the library runs a READ of
- * the group first.  Pass x = y = NULL for a WRITE without a token (prefill).
+ * at version v, the candidate being invisible until commit.  For fp32
+ * evidence, and for bf16 evidence with chunk <= 64, the token is fused into the
+ * update kernel, which reads the live state once for both; otherwise the
+ * library runs a READ of the group first.  Pass x = y = NULL for a WRITE without a token (prefill).
  *
  * With z == NULL the evidence rows come from the tail: the chunk is the
  * owner's tail_len rows followed by this step's own input x (the WRITE step

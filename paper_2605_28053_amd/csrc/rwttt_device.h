@@ -37,26 +37,6 @@ template <> struct Elem<uint16_t> {
   }
 };
 
-// N consecutive elements at p as floats; p is 8-byte (N*2 == 8) or 16-byte aligned.
-template <int N> __device__ __forceinline__ void load_n(const float* p, float (&v)[N]) {
-#pragma unroll
-  for (int i = 0; i < N; i += 4) {
-    const float4 t = *reinterpret_cast<const float4*>(p + i);
-    v[i] = t.x; v[i + 1] = t.y; v[i + 2] = t.z; v[i + 3] = t.w;
-  }
-}
-template <int N> __device__ __forceinline__ void load_n(const uint16_t* p, float (&v)[N]) {
-  if constexpr (N == 8) {
-    const uint4 t = *reinterpret_cast<const uint4*>(p);
-    v[0] = bf16_lo(t.x); v[1] = bf16_hi(t.x); v[2] = bf16_lo(t.y); v[3] = bf16_hi(t.y);
-    v[4] = bf16_lo(t.z); v[5] = bf16_hi(t.z); v[6] = bf16_lo(t.w); v[7] = bf16_hi(t.w);
-  } else {
-    static_assert(N == 4, "bf16 loads are 4 or 8 wide");
-    const uint2 t = *reinterpret_cast<const uint2*>(p);
-    v[0] = bf16_lo(t.x); v[1] = bf16_hi(t.x); v[2] = bf16_lo(t.y); v[3] = bf16_hi(t.y);
-  }
-}
-
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));

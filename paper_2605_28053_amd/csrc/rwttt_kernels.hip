@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "rwttt_kernels.h"
 
@@ -796,38 +797,147 @@ write_gemm_kernel(const WriteParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// WRITE, fp32 evidence: VALU rank-C update (fp32 products keep the small
-// tiny-config tolerance; bf16 operands would round Z and G)
+// WRITE, fp32 evidence: fp32 matrix instructions (bf16 operands would round Z
+// and G)
 // ---------------------------------------------------------------------------
+//
+// The update moves 2 |dW| bytes for 2C fp32 flop per element, so up to about
+// C = 100 it is bound by HBM and above by the fp32 matrix rate.  One block of
+// eight waves per (group slot, 256 / WN rows, 64 WN columns); a wave owns 32
+// rows and 64 columns.  v_mfma_f32_16x16x4_f32 takes its operands as they lie
+// in memory: lane (i, q) holds evidence row 4 s + q at state rows 2 i, 2 i + 1
+// (8 bytes of Z) and at columns 4 i .. 4 i + 3 (16 bytes of G), which are the
+// rows and columns i of 2 x 4 matrices; an accumulator register then belongs to
+// one state row, and a lane's four matrices to four consecutive columns of it.
+// So nothing goes through LDS, each lane updates 8 whole rows of 16 bytes, and
+// the live rows (and for the token W0's) are requested before the evidence.
+//
+// WN waves side by side make runs of 256 WN bytes per state row: WN = 4, 2 and
+// 1 take 126, 132 and 152 us for 8 owners of 12856 x 600, C = 17, and 66, 68 and
+// 71 us for two of 9728 x 2560, C = 4 (6.0 TB/s).  The token (x live + x W0, at
+// version v) is accumulated from the same live registers into one partial per
+// (owner, rows of a block), which read_reduce_kernel adds; the workspace has 64
+// such rows per owner, or one per READ chunk of 256 rows, so with a token WN is
+// 4 up to 4096 rows, 2 up to 8192 and 1 above.
+//
+// 4104 x 1032, C = 40, two owners with token (86 MB): 85 us before (a separate
+// READ, then one thread per four columns with a load for every fourth
+// product), 31 us now; without the token 21 us (68 MB).
 
-template <typename ST>
-__global__ void __launch_bounds__(256) write_valu_kernel(const WriteParams p) {
-  const int n4 = p.d_model / 4;
-  const size_t per_owner = size_t(p.d_ff) * n4;
-  const size_t gid = size_t(blockIdx.x) * 256 + threadIdx.x;
-  const int b = blockIdx.y;
-  if (gid >= per_owner) return;
-  const int m = int(gid / n4);
-  const int n = int(gid - size_t(m) * n4) * 4;
+constexpr int kFThreads = 512;           // 8 waves of 32 rows x 64 columns
+static_assert(kFThreads / 64 * 32 == kReadChunk, "WN = 1: one READ chunk per block");
+
+template <typename ST, bool TOKEN, int WN>
+__global__ void __launch_bounds__(kFThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
+write_f32_kernel(const WriteParams p) {
+  constexpr int QB = 4;                  // matrix steps (of four evidence rows) per group of loads
+  constexpr int WM = 8 / WN;             // waves one above the other
+  __shared__ float ysum[WM][64 * WN];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i16 = lane & 15, q4 = lane >> 4;
+  // block -> (XCD, position) -> ((rows, columns) pair, slot): the slots of one
+  // pair sit on one XCD, so that W0 comes from HBM once
+  const int xcd = blockIdx.x & 7;
+  const int pos = blockIdx.x >> 3;
+  const int pl = pos / p.count;
+  const int b = pos - pl * p.count;
+  const int pair = pl * 8 + xcd;
+  if (pair >= p.mt * p.ntl) return;
+  const int mt = pair / p.ntl;
+  const int nb = (pair - mt * p.ntl) * 64 * WN;
+  const int n0 = nb + (wave % WN) * 64;
+  const int mw = (mt * WM + wave / WN) * 32;             // the wave's first row
+  const int n = min(n0 + 4 * i16, p.d_model - 4);        // this lane's four columns
+  const int m = min(mw + 8 * q4, p.d_ff - 8);            // ... and eight rows, all inside or all outside
+  const bool ok = n0 + 4 * i16 < p.d_model && mw + 8 * q4 < p.d_ff;
   const float* Z = static_cast<const float*>(p.z[b]);
   const float* G = static_cast<const float*>(p.g[b]);
-  float a[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int c = 0; c < p.chunk; ++c) {
-    const float zc = Z[size_t(c) * p.d_ff + m];
-    const float4 g4 = *reinterpret_cast<const float4*>(G + size_t(c) * p.d_model + n);
-    a[0] = fmaf(zc, g4.x, a[0]);
-    a[1] = fmaf(zc, g4.y, a[1]);
-    a[2] = fmaf(zc, g4.z, a[2]);
-    a[3] = fmaf(zc, g4.w, a[3]);
-  }
-  const ST* live = static_cast<const ST*>(p.live[b]);
-  ST* shadow = static_cast<ST*>(p.shadow[b]);
-  float lv[4];
-  load_n<4>(live + size_t(m) * p.d_model + n, lv);
-  float out[4];
+
+  // row r of the eight is register r / 2 of matrix r % 2
+  const size_t at = size_t(m) * p.d_model + n;
+  const ST* live = static_cast<const ST*>(p.live[b]) + at;
+  Packed<ST, 4> lv[8];
+  Packed<float, 4> wv[TOKEN ? 8 : 1], xv[TOKEN ? 2 : 1];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) out[i] = lv[i] + p.eta * a[i];
-  store_n<4, true>(shadow + size_t(m) * p.d_model + n, out);
+  for (int r = 0; r < 8; ++r) load_packed<true>(live + size_t(r) * p.d_model, lv[r]);
+  if constexpr (TOKEN) {
+    const float* W0 = static_cast<const float*>(p.w0) + at;
+    const float* X = static_cast<const float*>(p.x) + size_t(p.row[b]) * p.d_ff + m;
+    load_packed<false>(X, xv[0]);
+    load_packed<false>(X + 4, xv[1]);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) load_packed<false>(W0 + size_t(r) * p.d_model, wv[r]);
+  }
+
+  // rows 2 i16, 2 i16 + 1 of the wave as the matrices' rows: past the matrix
+  // they are copies of real rows whose results are not stored
+  const uint32_t zoff = uint32_t(min(mw + 2 * i16, p.d_ff - 2)) * 4u, goff = uint32_t(n) * 4u;
+  f32x4_t acc[2][4];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[t][u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int nq = (p.chunk + 3) / 4;
+  for (int s0 = 0; s0 < nq; s0 += QB) {
+    Packed<float, 2> z[QB];
+    Packed<float, 4> g[QB];
+    const char* Zs = reinterpret_cast<const char*>(Z + size_t(4 * s0) * p.d_ff);
+    const char* Gs = reinterpret_cast<const char*>(G + size_t(4 * s0) * p.d_model);
+#pragma unroll
+    for (int s = 0; s < QB; ++s) {
+      const uint32_t c = uint32_t(min(4 * s + q4, p.chunk - 1 - 4 * s0));
+      load_packed<false>(reinterpret_cast<const float*>(Zs + (c * uint32_t(p.d_ff) * 4u + zoff)), z[s]);
+      load_packed<false>(reinterpret_cast<const float*>(Gs + (c * uint32_t(p.d_model) * 4u + goff)), g[s]);
+    }
+#pragma unroll
+    for (int s = 0; s < QB; ++s) {
+      if (s0 + s >= nq) break;
+      const bool in = 4 * (s0 + s) + q4 < p.chunk;       // rows past the chunk: both operands zero
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? z[s].get(t) : 0.f, in ? g[s].get(u) : 0.f,
+                                                           acc[t][u], 0, 0, 0);
+    }
+  }
+
+  ST* shadow = static_cast<ST*>(p.shadow[b]) + at;
+  float y[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    float o[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) o[u] = lv[r].get(u) + p.eta * acc[r & 1][u][r >> 1];
+    if (ok) store_n<4, true>(shadow + size_t(r) * p.d_model, o);
+    if constexpr (TOKEN) {
+      const float x = xv[r >> 2].get(r & 3);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) y[u] = fmaf(x, wv[r].get(u), fmaf(x, lv[r].get(u), y[u]));
+    }
+  }
+  if constexpr (TOKEN) {
+    // the four quarters' rows, then the waves one above the other, as trees
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float v = ok ? y[u] : 0.f;
+      v += __shfl_xor(v, 16);
+      v += __shfl_xor(v, 32);
+      if (q4 == 0) ysum[wave / WN][(wave % WN) * 64 + 4 * i16 + u] = v;
+    }
+    __syncthreads();
+    if (tid < 64 * WN && nb + tid < p.d_model) {
+      float v[WM];
+#pragma unroll
+      for (int w = 0; w < WM; ++w) v[w] = ysum[w][tid];
+#pragma unroll
+      for (int k = 1; k < WM; k *= 2)
+#pragma unroll
+        for (int w = 0; w + k < WM; w += 2 * k) v[w] += v[w + k];
+      p.tpart[(size_t(p.row[b]) * p.parts + mt) * p.npadw + nb + tid] = v[0];
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -927,8 +1037,53 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
     p.row[b] = in ? L.row[b] : 0u;
   }
   const bool token = L.x != nullptr;
-  if (L.io_bf16 && L.chunk <= kSMaxC) {
-    const ReadGeometry geo = read_geometry(L.d_ff, L.d_model, L.state_bf16, L.n_owners);
+  const ReadGeometry geo = read_geometry(L.d_ff, L.d_model, L.state_bf16, L.n_owners);
+  // the fused token's partials, p.parts rows of p.npadw per owner
+  auto reduce_token = [&] {
+    ReadParams q;
+    q.x = nullptr;
+    q.y = L.y;
+    q.w0 = nullptr;
+    q.part = p.tpart;
+    q.slot_part = 0;
+    q.count = L.count;
+    q.d_ff = L.d_ff;
+    q.d_model = L.d_model;
+    q.ks = p.parts;
+    q.nt = p.ntl;
+    q.npad = p.npadw;
+    for (int b = 0; b < RWTTT_MAX_GROUP; ++b) {
+      q.dw[b] = nullptr;
+      q.row[b] = b < L.count ? L.row[b] : 0u;
+      q.tail[b] = nullptr;
+    }
+    const dim3 grid((L.d_model + kRedCols - 1) / kRedCols, L.count);
+    if (L.io_bf16) hipLaunchKernelGGL((read_reduce_kernel<uint16_t>), grid, dim3(256), 0, stream, q);
+    else hipLaunchKernelGGL((read_reduce_kernel<float>), grid, dim3(256), 0, stream, q);
+  };
+  if (!L.io_bf16) {
+    auto run = [&](auto wn) {
+      constexpr int WN = decltype(wn)::value;
+      p.mt = p.parts = (L.d_ff * WN + kReadChunk - 1) / kReadChunk;
+      p.ntl = (L.d_model + 64 * WN - 1) / (64 * WN);
+      p.npadw = WN == 1 ? geo.npad : geo.tnpad;
+      const size_t at = WN == 1 ? 0 : geo.token_offset;
+      p.tpart = token ? reinterpret_cast<float*>(static_cast<char*>(L.workspace) + at) : nullptr;
+      const dim3 grid(unsigned((p.mt * p.ntl + 7) / 8 * 8) * unsigned(L.count));
+      if (token) {
+        hipLaunchKernelGGL((write_f32_kernel<ST, true, WN>), grid, dim3(kFThreads), 0, stream, p);
+        reduce_token();
+      } else {
+        hipLaunchKernelGGL((write_f32_kernel<ST, false, WN>), grid, dim3(kFThreads), 0, stream, p);
+      }
+    };
+    // without a token nothing limits the rows of a block
+    if (!token || L.d_ff * 4 <= kReadChunk * kSParts) run(std::integral_constant<int, 4>{});
+    else if (L.d_ff * 2 <= kReadChunk * kSParts) run(std::integral_constant<int, 2>{});
+    else run(std::integral_constant<int, 1>{});
+    return hipGetLastError();
+  }
+  if (L.chunk <= kSMaxC) {
     p.mt = (L.d_ff + kSTM - 1) / kSTM;
     p.ntl = (L.d_model + kSTN - 1) / kSTN;
     // partitions of an owner's row tiles: fixed by the shape, never by the group
@@ -939,25 +1094,7 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
     const dim3 grid(pairs8 * unsigned(L.count));
     if (token) {
       hipLaunchKernelGGL((write_stream_kernel<ST, true>), grid, dim3(256), 0, stream, p);
-      ReadParams q;
-      q.x = nullptr;
-      q.y = L.y;
-      q.w0 = nullptr;
-      q.part = p.tpart;
-      q.slot_part = 0;
-      q.count = L.count;
-      q.d_ff = L.d_ff;
-      q.d_model = L.d_model;
-      q.ks = p.parts;
-      q.nt = p.ntl;
-      q.npad = p.npadw;
-      for (int b = 0; b < RWTTT_MAX_GROUP; ++b) {
-        q.dw[b] = nullptr;
-        q.row[b] = b < L.count ? L.row[b] : 0u;
-        q.tail[b] = nullptr;
-      }
-      hipLaunchKernelGGL((read_reduce_kernel<uint16_t>), dim3((L.d_model + kRedCols - 1) / kRedCols, L.count),
-                         dim3(256), 0, stream, q);
+      reduce_token();
     } else {
       hipLaunchKernelGGL((write_stream_kernel<ST, false>), grid, dim3(256), 0, stream, p);
     }
@@ -981,22 +1118,15 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
       R.row[b] = L.row[b];
       R.tail[b] = nullptr;
     }
-    const hipError_t e = L.io_bf16 ? launch_read_t<uint16_t, ST>(R, stream)
-                                   : launch_read_t<float, ST>(R, stream);
+    const hipError_t e = launch_read_t<uint16_t, ST>(R, stream);
     if (e != hipSuccess) return e;
   }
-  if (L.io_bf16) {
-    p.mt = (L.d_ff + kGTM - 1) / kGTM;
-    p.ntl = (L.d_model + kGTN - 1) / kGTN;
-    const unsigned ntg = unsigned((p.ntl + kGColGroups - 1) / kGColGroups);
-    const unsigned mtq = unsigned((p.mt + kGRowClasses - 1) / kGRowClasses);
-    hipLaunchKernelGGL((write_gemm_kernel<ST>), dim3(unsigned(L.count) * mtq * ntg * 8u), dim3(kGThreads), 0,
-                       stream, p);
-  } else {
-    const size_t per_owner = size_t(L.d_ff) * (L.d_model / 4);
-    const unsigned bx = unsigned((per_owner + 255) / 256);
-    hipLaunchKernelGGL((write_valu_kernel<ST>), dim3(bx, L.count), dim3(256), 0, stream, p);
-  }
+  p.mt = (L.d_ff + kGTM - 1) / kGTM;
+  p.ntl = (L.d_model + kGTN - 1) / kGTN;
+  const unsigned ntg = unsigned((p.ntl + kGColGroups - 1) / kGColGroups);
+  const unsigned mtq = unsigned((p.mt + kGRowClasses - 1) / kGRowClasses);
+  hipLaunchKernelGGL((write_gemm_kernel<ST>), dim3(unsigned(L.count) * mtq * ntg * 8u), dim3(kGThreads), 0, stream,
+                     p);
   return hipGetLastError();
 }
 

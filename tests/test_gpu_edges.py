@@ -80,3 +80,53 @@ def test_adapter_write_keeps_non_finite_evidence_in_its_place():
     assert not torch.isfinite(b[:, 135]).any()
     assert torch.isfinite(b[:, :135]).all()
     assert write_group(sess, [0], 0, 19, [zd], [gd]) == R.RWTTT_E_DIRTY
+
+
+# fp32 evidence: the smallest matrix, one block of 256 x 64 and one row or
+# column group past it, ragged waves; chunk: one, around a matrix step of 4 and
+# a group of 16, a long one; rows: the last with 64, the first with 128 and with
+# 256 rows per partial of the token
+F32_WRITES = [
+    (4096, 264, "f32", 2), (4104, 136, "f32", 3), (8200, 72, "f32", 6),
+    (8, 8, "f32", 1), (256, 64, "f32", 4), (264, 72, "bf16", 5), (248, 56, "f32", 15), (512, 136, "bf16", 16),
+    (776, 200, "f32", 17), (1032, 1032, "f32", 130),
+]
+
+
+@pytest.mark.parametrize("token", [True, False])
+@pytest.mark.parametrize("d_ff,d_model,state,chunk", F32_WRITES)
+def test_f32_write_edges(d_ff, d_model, state, chunk, token):
+    wl = small_workload(d_ff, d_model, "f32", state, 3)
+    say("f32 write edge", d_ff, d_model, state, chunk, token)
+    src = TensorSource(wl)
+    sess = Session(wl, src, tail_rows=0)
+    group = [2, 0]
+    ev = [evidence(wl, chunk, r) for r in group]
+    X = draw((3, d_ff), 1.0, "f32", wl.seed, (63, chunk))
+    xd = to_device(X, "f32")
+    y = torch.full((3, d_model), 7.0, device="cuda")
+    st = write_group(sess, group, 0, chunk, [to_device(z, "f32") for z, _ in ev],
+                     [to_device(g, "f32") for _, g in ev], None, *((xd, y) if token else ()))
+    assert st == R.RWTTT_OK
+    torch.cuda.synchronize()
+    W0 = O.widen(src.w0(0), "f32")
+    for r, (Z, G) in zip(group, ev):
+        D = O.widen(src.dw_init(r, 0), state)
+        want = O.write_candidate(D, O.widen(Z, "f32"), O.widen(G, "f32"), wl.eta)
+        assert rel_norm(host_f64(sess.shadow(r, 0), state), want) <= norm_tol(state), r
+        if token:
+            assert rel_norm(host_f64(y[r], "f32"), O.read_apply(O.widen(X[r], "f32"), W0, D)) <= 1e-6, r
+    assert torch.all(y[1] == 7.0) and (token or torch.all(y == 7.0))
+
+
+def test_f32_write_keeps_non_finite_evidence_in_its_place():
+    wl = small_workload(264, 72, "f32", "f32", 1)
+    sess = Session(wl, TensorSource(wl), tail_rows=0)
+    Z, G = evidence(wl, 5, 0)
+    zd, gd = to_device(Z, "f32"), to_device(G, "f32")
+    zd[4, 263], gd[4, 71] = float("inf"), float("nan")
+    assert write_group(sess, [0], 0, 5, [zd], [gd]) == R.RWTTT_OK
+    bad = ~torch.isfinite(sess.shadow(0, 0))
+    want = torch.zeros_like(bad)
+    want[263, :] = want[:, 71] = True
+    assert torch.equal(bad, want)
