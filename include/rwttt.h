@@ -184,7 +184,7 @@ rwttt_status rwttt_plan(const rwttt_ctx* ctx, const rwttt_event* ev, uint32_t n_
  * are bit-identical whatever the group's size, order or other members.
  * An empty group returns RWTTT_OK and launches nothing.  Launches two kernels
  * on `stream` (split-K partial sums into the owners' workspace regions, then
- * their reduction).  Reads and writes of one context may run concurrently on
+ * their reduction), or one for few rows (d_ff <= 1536) and little state.  Reads and writes of one context may run concurrently on
  * different streams when they name disjoint owners (the serving contract
  * gives each owner one transition per step); calls that share an owner must
  * be ordered on the device (same stream, or an event wait).

@@ -130,3 +130,39 @@ def test_f32_write_keeps_non_finite_evidence_in_its_place():
     want = torch.zeros_like(bad)
     want[263, :] = want[:, 71] = True
     assert torch.equal(bad, want)
+
+
+# READs of up to 1536 rows run as one launch for 36 MB of state and W0, as two
+# above: a group on each side must give an owner the same bits.  Rows: one leaf
+# of 8, one leaf per row group (1024) and past it, the limit and past it (always
+# two launches); the last column tile is ragged
+READ_ROUTES = [
+    (264, 4104, "bf16", "f32", 12), (1024, 2056, "bf16", "bf16", 9), (1032, 2056, "bf16", "f32", 5),
+    (1536, 1032, "f32", "f32", 8), (1544, 1032, "bf16", "f32", 8), (3600, 520, "f32", "bf16", 3),
+    (8, 8, "f32", "f32", 2), (16, 72, "bf16", "f32", 3),
+]
+
+
+@pytest.mark.parametrize("d_ff,d_model,io,state,n", READ_ROUTES)
+def test_read_routes_agree_bit_for_bit(d_ff, d_model, io, state, n):
+    wl = small_workload(d_ff, d_model, io, state, n)
+    say("read route", d_ff, d_model, io, state, n)
+    src = TensorSource(wl)
+    sess = Session(wl, src, tail_rows=2)
+    X = draw((n, d_ff), 1.0, io, wl.seed, (64, n))
+    xd = to_device(X, io)
+    group = list(range(n))[::-1]
+    y = [torch.full((n, d_model), 7.0, device="cuda", dtype=xd.dtype) for _ in range(2)]
+    read_group(sess, group, 0, xd, y[0])
+    for r in range(n):                                       # alone, with the tail append
+        st = R.rwttt_read_append(sess.ctx, R.make_group(R.RWTTT_READ, 0, 1), R.u32_array([r]), 0, xd.data_ptr(),
+                                 y[1].data_ptr(), torch.cuda.current_stream().cuda_stream)
+        assert st == R.RWTTT_OK
+    torch.cuda.synchronize()
+    assert torch.equal(y[0], y[1])
+    for r in range(n):
+        assert torch.equal(sess.tails[r][0][0], xd[r]) and not sess.tails[r][0][1].any()
+    W0 = O.widen(src.w0(0), io)
+    for r in (0, n - 1):
+        want = O.read_apply(O.widen(X[r], io), W0, O.widen(src.dw_init(r, 0), state))
+        assert rel_norm(host_f64(y[0][r], io), want) <= norm_tol(io), r
