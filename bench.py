@@ -201,8 +201,8 @@ class LaunchTimer:
 
 
 def fused_token(wl, chunk):
-    """Whether a WRITE with its token runs as one fused kernel (bf16 evidence, C <= 64)."""
-    return wl.io_dtype == "bf16" and chunk <= 64
+    """Whether a WRITE with its token runs as one fused kernel (fp32 evidence, or bf16 with C <= 64)."""
+    return wl.io_dtype != "bf16" or chunk <= 64
 
 
 def write_kernel_name(wl, chunk, rank=0):
@@ -210,7 +210,9 @@ def write_kernel_name(wl, chunk, rank=0):
         return "adapter_pq_kernel+adapter_update_kernel"
     if wl.io_dtype != "bf16":
         return "write_f32_kernel"
-    return "write_stream_kernel" if chunk <= 64 else "write_gemm_kernel"
+    if chunk <= 64:       # with its token, as every decode WRITE of the workloads
+        return "write_stream_kernel"
+    return "write_rows_kernel" if wl.state_dtype == "f32" and chunk <= 384 else "write_gemm_kernel"
 
 
 def items_fn(wl):

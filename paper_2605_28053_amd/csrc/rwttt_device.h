@@ -83,8 +83,11 @@ template <typename T, int N> struct Packed {
 template <bool NT, typename T, int N>
 __device__ __forceinline__ void load_packed(const T* p, Packed<T, N>& r) {
   constexpr int W = Packed<T, N>::W;
-  static_assert(W == 2 || W % 4 == 0, "8- or 16-byte multiples");
-  if constexpr (W == 2) {
+  static_assert(W == 1 || W == 2 || W % 4 == 0, "4 or 8 bytes, or a multiple of 16");
+  if constexpr (W == 1) {
+    const uint32_t* q = reinterpret_cast<const uint32_t*>(p);
+    r.w[0] = NT ? __builtin_nontemporal_load(q) : *q;
+  } else if constexpr (W == 2) {
     const u32x2_t t = NT ? __builtin_nontemporal_load(reinterpret_cast<const u32x2_t*>(p))
                          : *reinterpret_cast<const u32x2_t*>(p);
     r.w[0] = t[0];

@@ -94,6 +94,21 @@ __device__ __forceinline__ void tree_push(float (&stack)[N][COLS], int i, const 
       for (int c = 0; c < COLS; ++c) stack[k][c] = t[c];
 }
 
+// Whether the live state that a call reads is little enough to leave in the 256
+// MB last-level cache for the calls after it: loaded without the non-temporal
+// hint it stays there, several such states beside each other, and a later call
+// finds it.  In us without / with the hint, calls on three states in turn, then
+// on six (so that the last-level cache is too small): READ of four owners of 2048
+// x 2048 bf16 (42 MB) 11.8 / 16.4, 15.4 / 16.5; WRITE of two of 3072 x 1024
+// (25 MB) 9.0 / 10.3, 9.0 / 10.6, of eight of 600 x 2000 (38 MB) 14.8 / 19.7,
+// 18.6 / 20.0.  Above, the states push each other out and the hint is better:
+// READ of one owner of 9728 x 2560 (149 MB) 31.8 / 27.4 us, and a large READ
+// would push W0 out of L2 (eight owners 147 / 128 us).  Stores always have the
+// hint: a candidate kept in the cache takes the place of a live state (one WRITE
+// of 9728 x 2560, C = 64, 54.6 against 48.1 us).  The GEMM keeps it for its live tiles too: its evidence lives
+// in L2 (62.2 against 59.6 us for 11 owners of 5448 x 288 bf16, C = 650).
+inline bool stays_cached(size_t live_bytes) { return live_bytes <= 48000000; }
+
 // Balanced tree over N (a power of two) values in index order.
 template <int N> __device__ __forceinline__ float tree_sum(float (&v)[N]) {
 #pragma unroll
@@ -103,7 +118,7 @@ template <int N> __device__ __forceinline__ float tree_sum(float (&v)[N]) {
   return v[0];
 }
 
-template <typename IO, typename ST, int NW, int LEAF>
+template <typename IO, typename ST, int NW, int LEAF, bool NT>
 __global__ void __launch_bounds__(64 * NW) read_partial_kernel(const ReadParams p) {
   constexpr int COLS = 16 / sizeof(ST);
   constexpr int TILE_N = 64 * COLS;
@@ -159,7 +174,7 @@ __global__ void __launch_bounds__(64 * NW) read_partial_kernel(const ReadParams 
       Packed<IO, COLS> w[kUnroll];
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
-        load_packed<true>(dbase + size_t(k + u) * p.d_model, v[u]);
+        load_packed<NT>(dbase + size_t(k + u) * p.d_model, v[u]);
         load_packed<false>(wbase + size_t(k + u) * p.d_model, w[u]);
       }
 #pragma unroll
@@ -286,7 +301,7 @@ __global__ void __launch_bounds__(kDirectThreads) read_direct_kernel(const ReadP
 #pragma unroll
       for (int u = 0; u < kDirectLeaf; ++u) {
         xv[u] = Elem<IO>::get(x, k + u);
-        load_packed<true>(d + size_t(k + u) * p.d_model, v[u]);
+        load_packed<false>(d + size_t(k + u) * p.d_model, v[u]);
         load_packed<false>(w0 + size_t(k + u) * p.d_model, w[u]);
       }
 #pragma unroll
@@ -337,7 +352,7 @@ struct WriteParams {
 };
 
 // ---------------------------------------------------------------------------
-// WRITE, bf16 evidence, small chunk (C <= 64): streaming rank-C update
+// WRITE with a token, bf16 evidence, small chunk (C <= 64): streaming rank-C update
 // ---------------------------------------------------------------------------
 //
 // For C <= 64 the update moves 2 x |dW| bytes for only 2C flop per element,
@@ -353,7 +368,7 @@ struct WriteParams {
 // wave reads, updates and stores whole 1 KB rows of the slot.  No load is on
 // the critical path of the item that issues it.
 //
-// With a fused token (the WRITE step's own output, read at version v before
+// For the fused token (the WRITE step's own output, read at version v before
 // the candidate is committed) the block also loads the same rows of W0 and
 // accumulates x[m] * live[m] + x[m] * W0[m] over its items: the live state is
 // read once for both the token and the update.  Per-(owner, partition)
@@ -422,7 +437,7 @@ __device__ __forceinline__ void stream_store_pair(uint16_t* dst, int tid, int ro
   }
 }
 
-template <typename ST, bool TOKEN>
+template <typename ST, bool NT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 write_stream_kernel(const WriteParams p) {
   constexpr int RPW = kSTM / 4;           // epilogue rows per wave
@@ -471,13 +486,11 @@ write_stream_kernel(const WriteParams p) {
   Packed<ST, 4> lv[RPW];
   Packed<uint16_t, 4> wv[RPW];
   uint4 za, zb, xq = make_uint4(0, 0, 0, 0);
-  stream_load_rows(live, p.d_ff, p.d_model, part * kSTM, wave, ncol, ncol_ok, lv);
+  stream_load_rows<NT>(live, p.d_ff, p.d_model, part * kSTM, wave, ncol, ncol_ok, lv);
   stream_load_pair(Z, p.d_ff, p.d_ff, p.chunk, part * kSTM, tid, za, zb);
-  if (TOKEN) {
-    stream_load_rows<false>(W0, p.d_ff, p.d_model, part * kSTM, wave, ncol, ncol_ok, wv);
-    if (part * kSTM + wave * RPW < p.d_ff)
-      xq = *reinterpret_cast<const uint4*>(X + part * kSTM + wave * RPW);
-  }
+  stream_load_rows<false>(W0, p.d_ff, p.d_model, part * kSTM, wave, ncol, ncol_ok, wv);
+  if (part * kSTM + wave * RPW < p.d_ff)
+    xq = *reinterpret_cast<const uint4*>(X + part * kSTM + wave * RPW);
 #pragma unroll
   for (int j = 0; j < kSTN / 32; ++j) stream_store_pair(gt, tid, j * 32, ga[j], gb[j]);
 
@@ -491,13 +504,11 @@ write_stream_kernel(const WriteParams p) {
     Packed<uint16_t, 4> nw[RPW];
     uint4 nxq = make_uint4(0, 0, 0, 0);
     if (mn < p.mt) {
-      stream_load_rows(live, p.d_ff, p.d_model, mn * kSTM, wave, ncol, ncol_ok, nx);
+      stream_load_rows<NT>(live, p.d_ff, p.d_model, mn * kSTM, wave, ncol, ncol_ok, nx);
       stream_load_pair(Z, p.d_ff, p.d_ff, p.chunk, mn * kSTM, tid, za, zb);
-      if (TOKEN) {
-        stream_load_rows<false>(W0, p.d_ff, p.d_model, mn * kSTM, wave, ncol, ncol_ok, nw);
-        if (mn * kSTM + wave * RPW < p.d_ff)
-          nxq = *reinterpret_cast<const uint4*>(X + mn * kSTM + wave * RPW);
-      }
+      stream_load_rows<false>(W0, p.d_ff, p.d_model, mn * kSTM, wave, ncol, ncol_ok, nw);
+      if (mn * kSTM + wave * RPW < p.d_ff)
+        nxq = *reinterpret_cast<const uint4*>(X + mn * kSTM + wave * RPW);
     }
     f32x16_t acc[2] = {f32x16_t{}, f32x16_t{}};
 #pragma unroll
@@ -531,39 +542,35 @@ write_stream_kernel(const WriteParams p) {
         store_n<4, true>(shadow + size_t(m) * p.d_model + ncol, o);
       }
     }
-    if (TOKEN) {
-      // token: x[m] * live[m] + x[m] * W0[m] over this wave's rows, in row order
-      const uint32_t xw[4] = {xq.x, xq.y, xq.z, xq.w};
+    // token: x[m] * live[m] + x[m] * W0[m] over this wave's rows, in row order
+    const uint32_t xw[4] = {xq.x, xq.y, xq.z, xq.w};
 #pragma unroll
-      for (int rr = 0; rr < RPW; ++rr) {
-        const float xv = (rr & 1) ? bf16_hi(xw[rr >> 1]) : bf16_lo(xw[rr >> 1]);
+    for (int rr = 0; rr < RPW; ++rr) {
+      const float xv = (rr & 1) ? bf16_hi(xw[rr >> 1]) : bf16_lo(xw[rr >> 1]);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) yacc[c] = fmaf(xv, wv[rr].get(c), fmaf(xv, lv[rr].get(c), yacc[c]));
-      }
+      for (int c = 0; c < 4; ++c) yacc[c] = fmaf(xv, wv[rr].get(c), fmaf(xv, lv[rr].get(c), yacc[c]));
     }
     if (mn < p.mt) {
 #pragma unroll
       for (int rr = 0; rr < RPW; ++rr) {
         lv[rr] = nx[rr];
-        if (TOKEN) wv[rr] = nw[rr];
+        wv[rr] = nw[rr];
       }
       xq = nxq;
     }
     __syncthreads();
   }
 
-  if (TOKEN) {
-    // the four waves' token sums in wave order -> one partial per (owner, partition)
+  // the four waves' token sums in wave order -> one partial per (owner, partition)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) out[wave * kSTN + lane * 4 + c] = yacc[c];
-    __syncthreads();
-    const float v = ((out[tid] + out[kSTN + tid]) + out[2 * kSTN + tid]) + out[3 * kSTN + tid];
-    p.tpart[(size_t(p.row[b]) * p.parts + part) * p.npadw + n0 + tid] = v;
-  }
+  for (int c = 0; c < 4; ++c) out[wave * kSTN + lane * 4 + c] = yacc[c];
+  __syncthreads();
+  const float v = ((out[tid] + out[kSTN + tid]) + out[2 * kSTN + tid]) + out[3 * kSTN + tid];
+  p.tpart[(size_t(p.row[b]) * p.parts + part) * p.npadw + n0 + tid] = v;
 }
 
 // ---------------------------------------------------------------------------
-// WRITE, bf16 evidence, large chunk (C > 64): tiled GEMM
+// WRITE, bf16 evidence, bf16 state or large chunk: tiled GEMM
 // ---------------------------------------------------------------------------
 //
 // At C = 512 the update does 2C flop per state element and is near the MFMA
@@ -971,12 +978,13 @@ write_gemm_kernel(const WriteParams p) {
 //
 // 4104 x 1032, C = 40, two owners with token (86 MB): 85 us before (a separate
 // READ, then one thread per four columns with a load for every fourth
-// product), 31 us now; without the token 21 us (68 MB).
+// product), 29 us now (32 when the state comes from HBM); without the token 21 us
+// (68 MB).
 
 constexpr int kFThreads = 512;           // 8 waves of 32 rows x 64 columns
 static_assert(kFThreads / 64 * 32 == kReadChunk, "WN = 1: one READ chunk per block");
 
-template <typename ST, bool TOKEN, int WN>
+template <typename ST, bool TOKEN, int WN, bool NT>
 __global__ void __launch_bounds__(kFThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 write_f32_kernel(const WriteParams p) {
   constexpr int QB = 4;                  // matrix steps (of four evidence rows) per group of loads
@@ -1009,7 +1017,7 @@ write_f32_kernel(const WriteParams p) {
   Packed<ST, 4> lv[8];
   Packed<float, 4> wv[TOKEN ? 8 : 1], xv[TOKEN ? 2 : 1];
 #pragma unroll
-  for (int r = 0; r < 8; ++r) load_packed<true>(live + size_t(r) * p.d_model, lv[r]);
+  for (int r = 0; r < 8; ++r) load_packed<NT>(live + size_t(r) * p.d_model, lv[r]);
   if constexpr (TOKEN) {
     const float* W0 = static_cast<const float*>(p.w0) + at;
     const float* X = static_cast<const float*>(p.x) + size_t(p.row[b]) * p.d_ff + m;
@@ -1086,6 +1094,122 @@ write_f32_kernel(const WriteParams p) {
         for (int w = 0; w + k < WM; w += 2 * k) v[w] += v[w + k];
       p.tpart[(size_t(p.row[b]) * p.parts + mt) * p.npadw + nb + tid] = v[0];
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// WRITE, bf16 evidence, fp32 state, C <= 384, token apart: register operands
+// ---------------------------------------------------------------------------
+//
+// The fp32 state moves 8 bytes per element for 2C flop, so it is bound by HBM
+// over this whole range; what is wanted is a copy that multiplies on the side.
+// As in write_f32_kernel nothing goes through LDS and a lane updates whole
+// rows: a wave owns 64 rows x 64 columns, a lane (i, q) loads four consecutive
+// evidence rows 4 q .. 4 q + 3 of a group of 16 at state rows 4 i .. 4 i + 3 (8
+// bytes of Z each) and at columns 4 i .. 4 i + 3 (of G), and byte permutes turn
+// these 4 x 4 blocks into the operands (four consecutive ranks of one row or
+// column) of 4 x 4 matrices of v_mfma_f32_16x16x16_bf16.  The waves are
+// independent; four neighbours of a row of tiles make a block (waves one by
+// one: 112 against 104 us below), three blocks fit a CU.
+//
+// Three owners of 9728 x 2560 (602 MB + evidence), in us, against the streaming
+// kernel (C <= 64) and the GEMM that took these calls before: 104 / 117 at C =
+// 64, 114 / 155 at 128, 137 / 165 at 256, 168 / 177 at 384.  The evidence loads
+// bind then (200 / 188 at 512), so longer chunks stay with the GEMM.  One
+// owner of 2496 x 824, C = 159: 8.7 / 15.4.  Half as many state rows per wave
+// needs nearly twice the loads per product (108, 125, 167 at 64, 128, 256).
+// With bf16 state, half the bytes, the GEMM is as fast at C = 16 (78 / 80 us
+// for two owners of 14336 x 4096) and faster above (94 / 82 at C = 64); it also
+// takes the bf16 chunks up to 64 that the streaming kernel had (four owners of
+// 9728 x 2560, C = 32: 71 / 83 us).
+
+constexpr int kRThreads = 256;           // 4 waves, neighbours in a row of tiles
+constexpr int kRTM = 64;                 // rows per wave
+constexpr int kRTN = 64;                 // columns per wave
+constexpr int kRMaxC = 384;              // largest chunk on this path
+
+template <bool NT>
+__global__ void __launch_bounds__(kRThreads) __attribute__((amdgpu_waves_per_eu(3, 3)))
+write_rows_kernel(const WriteParams p) {
+  constexpr int RS = 16;                 // evidence rows per matrix step
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  const int i16 = lane & 15, q4 = lane >> 4;
+  const int b = blockIdx.y;
+  // blocks are dealt to the XCDs round-robin: each round of eight is rotated by
+  // one, or a power of two of columns would give an XCD always the same ones
+  // (30.4 against 24.2 us for two owners of 8192 x 1024)
+  const int bx = (int(blockIdx.x) & ~7) | ((int(blockIdx.x) + (int(blockIdx.x) >> 3)) & 7);
+  const int tile = bx * (kRThreads / 64) + wave;         // the waves are independent
+  const int mt = tile / p.ntl;
+  if (mt >= p.mt) return;
+  const int m0 = mt * kRTM + 16 * q4;                    // this lane's 16 rows: two runs of eight, each
+                                                         // inside or outside the matrix as a whole
+  const int n0 = (tile - mt * p.ntl) * kRTN + 4 * i16;
+  const bool n_ok = n0 < p.d_model;
+  const int n = min(n0, p.d_model - 4);                  // ... and four columns
+  const uint16_t* Z = static_cast<const uint16_t*>(p.z[b]);
+  const uint16_t* G = static_cast<const uint16_t*>(p.g[b]);
+
+  // the live rows are requested first: row r is register r / 4 of matrix r % 4
+  Packed<float, 4> lv[16];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const float* live = static_cast<const float*>(p.live[b]) + size_t(min(m0 + 8 * h, p.d_ff - 8)) * p.d_model + n;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) load_packed<NT>(live + size_t(r) * p.d_model, lv[8 * h + r]);
+  }
+
+  const uint32_t zoff = uint32_t(min(mt * kRTM + 4 * i16, p.d_ff - 4)) * 2u, goff = uint32_t(n) * 2u;
+  f32x4_t acc[4][4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[t][u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int c0 = 0; c0 < p.chunk; c0 += RS) {
+    Packed<uint16_t, 4> z[4], g[4];
+    const char* Zs = reinterpret_cast<const char*>(Z + size_t(c0) * p.d_ff);
+    const char* Gs = reinterpret_cast<const char*>(G + size_t(c0) * p.d_model);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t c = uint32_t(min(4 * q4 + i, p.chunk - 1 - c0)) * 2u;
+      load_packed<false>(reinterpret_cast<const uint16_t*>(Zs + (c * uint32_t(p.d_ff) + zoff)), z[i]);
+      load_packed<false>(reinterpret_cast<const uint16_t*>(Gs + (c * uint32_t(p.d_model) + goff)), g[i]);
+    }
+    if (c0 + RS > p.chunk) {
+      // rows past the chunk: both operands zero
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (c0 + 4 * q4 + i >= p.chunk) {
+          z[i].zero();
+          g[i].zero();
+        }
+    }
+    // value j of four evidence rows in one operand
+    auto pick = [](const Packed<uint16_t, 4> (&v)[4], int j) {
+      const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
+      const int w = j >> 1;
+      return __builtin_bit_cast(i16x4_t, u32x2_t{__builtin_amdgcn_perm(v[1].w[w], v[0].w[w], sel),
+                                                 __builtin_amdgcn_perm(v[3].w[w], v[2].w[w], sel)});
+    };
+    i16x4_t az[4], bg[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) az[t] = pick(z, t);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) bg[u] = pick(g, u);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(az[t], bg[u], acc[t][u], 0, 0, 0);
+  }
+
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    float o[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) o[u] = lv[r].get(u) + p.eta * acc[r & 3][u][r >> 2];
+    if (n_ok && m0 + (r & 8) < p.d_ff)
+      store_n<4, true>(static_cast<float*>(p.shadow[b]) + size_t(m0 + r) * p.d_model + n, o);
   }
 }
 
@@ -1177,12 +1301,17 @@ hipError_t launch_read_t(const ReadLaunch& L, hipStream_t stream, float* slot_pa
   // leaves of eight rows where the one launch above must match, and for fp32 io
   // with bf16 state, where they are faster (20.0 against 23.4 us for two owners
   // of 3600 x 1512)
-  if (L.d_ff <= kDirectRows || sizeof(IO) > sizeof(ST))
-    hipLaunchKernelGGL((read_partial_kernel<IO, ST, 8, kDirectLeaf>), grid, dim3(512), 0, stream, p);
-  else if (L.count == 1)
-    hipLaunchKernelGGL((read_partial_kernel<IO, ST, 4, 32>), grid, dim3(256), 0, stream, p);
-  else
-    hipLaunchKernelGGL((read_partial_kernel<IO, ST, 8, 32>), grid, dim3(512), 0, stream, p);
+  auto run = [&](auto nt) {
+    constexpr bool NT = decltype(nt)::value;
+    if (L.d_ff <= kDirectRows || sizeof(IO) > sizeof(ST))
+      hipLaunchKernelGGL((read_partial_kernel<IO, ST, 8, kDirectLeaf, NT>), grid, dim3(512), 0, stream, p);
+    else if (L.count == 1)
+      hipLaunchKernelGGL((read_partial_kernel<IO, ST, 4, 32, NT>), grid, dim3(256), 0, stream, p);
+    else
+      hipLaunchKernelGGL((read_partial_kernel<IO, ST, 8, 32, NT>), grid, dim3(512), 0, stream, p);
+  };
+  if (stays_cached(bytes)) run(std::false_type{});
+  else run(std::true_type{});
   launch_reduce<IO>(p, L.d_ff <= kDirectRows, stream);
   return hipGetLastError();
 }
@@ -1209,6 +1338,7 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
     p.row[b] = in ? L.row[b] : 0u;
   }
   const bool token = L.x != nullptr;
+  const bool cached = stays_cached(size_t(L.d_ff) * L.d_model * L.count * sizeof(ST));
   const ReadGeometry geo = read_geometry(L.d_ff, L.d_model, L.state_bf16, L.n_owners);
   // the fused token's partials, p.parts rows of p.npadw per owner
   auto reduce_token = [&] {
@@ -1233,8 +1363,9 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
     else launch_reduce<float>(q, false, stream);
   };
   if (!L.io_bf16) {
-    auto run = [&](auto wn) {
+    auto run = [&](auto wn, auto nt) {
       constexpr int WN = decltype(wn)::value;
+      constexpr bool NT = decltype(nt)::value;
       p.mt = p.parts = (L.d_ff * WN + kReadChunk - 1) / kReadChunk;
       p.ntl = (L.d_model + 64 * WN - 1) / (64 * WN);
       p.npadw = WN == 1 ? geo.npad : geo.tnpad;
@@ -1242,33 +1373,35 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
       p.tpart = token ? reinterpret_cast<float*>(static_cast<char*>(L.workspace) + at) : nullptr;
       const dim3 grid(unsigned((p.mt * p.ntl + 7) / 8 * 8) * unsigned(L.count));
       if (token) {
-        hipLaunchKernelGGL((write_f32_kernel<ST, true, WN>), grid, dim3(kFThreads), 0, stream, p);
+        hipLaunchKernelGGL((write_f32_kernel<ST, true, WN, NT>), grid, dim3(kFThreads), 0, stream, p);
         reduce_token();
       } else {
-        hipLaunchKernelGGL((write_f32_kernel<ST, false, WN>), grid, dim3(kFThreads), 0, stream, p);
+        hipLaunchKernelGGL((write_f32_kernel<ST, false, WN, NT>), grid, dim3(kFThreads), 0, stream, p);
       }
     };
-    // without a token nothing limits the rows of a block
-    if (!token || L.d_ff * 4 <= kReadChunk * kSParts) run(std::integral_constant<int, 4>{});
-    else if (L.d_ff * 2 <= kReadChunk * kSParts) run(std::integral_constant<int, 2>{});
-    else run(std::integral_constant<int, 1>{});
+    auto by_rows = [&](auto nt) {
+      // without a token nothing limits the rows of a block
+      if (!token || L.d_ff * 4 <= kReadChunk * kSParts) run(std::integral_constant<int, 4>{}, nt);
+      else if (L.d_ff * 2 <= kReadChunk * kSParts) run(std::integral_constant<int, 2>{}, nt);
+      else run(std::integral_constant<int, 1>{}, nt);
+    };
+    if (cached) by_rows(std::false_type{});
+    else by_rows(std::true_type{});
     return hipGetLastError();
   }
-  if (L.chunk <= kSMaxC) {
+  if (L.chunk <= kSMaxC && token) {
     p.mt = (L.d_ff + kSTM - 1) / kSTM;
     p.ntl = (L.d_model + kSTN - 1) / kSTN;
     // partitions of an owner's row tiles: fixed by the shape, never by the group
     p.parts = std::min(stream_parts(L.d_ff, L.d_model), geo.tparts);
     p.npadw = geo.tnpad;
-    p.tpart = token ? reinterpret_cast<float*>(static_cast<char*>(L.workspace) + geo.token_offset) : nullptr;
-    const unsigned pairs8 = unsigned((p.ntl * p.parts + 7) / 8 * 8);
-    const dim3 grid(pairs8 * unsigned(L.count));
-    if (token) {
-      hipLaunchKernelGGL((write_stream_kernel<ST, true>), grid, dim3(256), 0, stream, p);
-      reduce_token();
-    } else {
+    p.tpart = reinterpret_cast<float*>(static_cast<char*>(L.workspace) + geo.token_offset);
+    const dim3 grid(unsigned((p.ntl * p.parts + 7) / 8 * 8) * unsigned(L.count));
+    if (cached)
       hipLaunchKernelGGL((write_stream_kernel<ST, false>), grid, dim3(256), 0, stream, p);
-    }
+    else
+      hipLaunchKernelGGL((write_stream_kernel<ST, true>), grid, dim3(256), 0, stream, p);
+    reduce_token();
     return hipGetLastError();
   }
   if (token) {
@@ -1292,12 +1425,23 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
     const hipError_t e = launch_read_t<uint16_t, ST>(R, stream);
     if (e != hipSuccess) return e;
   }
+  if (!L.state_bf16 && L.chunk <= kRMaxC) {
+    p.mt = (L.d_ff + kRTM - 1) / kRTM;
+    p.ntl = (L.d_model + kRTN - 1) / kRTN;
+    constexpr int waves = kRThreads / 64;
+    const dim3 grid(unsigned((p.mt * p.ntl + waves - 1) / waves + 7) / 8 * 8, unsigned(L.count));
+    if (cached)
+      hipLaunchKernelGGL((write_rows_kernel<false>), grid, dim3(kRThreads), 0, stream, p);
+    else
+      hipLaunchKernelGGL((write_rows_kernel<true>), grid, dim3(kRThreads), 0, stream, p);
+    return hipGetLastError();
+  }
   p.mt = (L.d_ff + kGTM - 1) / kGTM;
   p.ntl = (L.d_model + kGTN - 1) / kGTN;
   const unsigned ntg = unsigned((p.ntl + kGColGroups - 1) / kGColGroups);
   const unsigned mtq = unsigned((p.mt + kGRowClasses - 1) / kGRowClasses);
-  hipLaunchKernelGGL((write_gemm_kernel<ST>), dim3(unsigned(L.count) * mtq * ntg * 8u), dim3(kGThreads), 0, stream,
-                     p);
+  const dim3 grid(unsigned(L.count) * mtq * ntg * 8u);
+  hipLaunchKernelGGL((write_gemm_kernel<ST>), grid, dim3(kGThreads), 0, stream, p);
   return hipGetLastError();
 }
 

@@ -166,3 +166,48 @@ def test_read_routes_agree_bit_for_bit(d_ff, d_model, io, state, n):
     for r in (0, n - 1):
         want = O.read_apply(O.widen(X[r], io), W0, O.widen(src.dw_init(r, 0), state))
         assert rel_norm(host_f64(y[0][r], io), want) <= norm_tol(io), r
+
+
+# bf16 evidence without a token.  fp32 state, register operands: the smallest
+# matrix, a tile of 64 x 64 and its remainders (8 rows in a lane's second run,
+# one column group past the tile), a count of tiles no block of four divides;
+# chunk: one, a group of 16 and past it, the last of this path and the first of
+# the GEMM.  bf16 state, GEMM: chunks of one and two stages of 32 ranks
+ROWS_WRITES = [
+    (8, 8, "f32", 1), (64, 64, "f32", 16), (72, 72, "f32", 17), (136, 328, "f32", 33), (248, 1032, "f32", 64),
+    (520, 264, "f32", 384), (520, 264, "f32", 385), (8, 8, "bf16", 1), (264, 136, "bf16", 31), (520, 136, "bf16", 33),
+    (264, 264, "bf16", 64),
+]
+
+
+@pytest.mark.parametrize("d_ff,d_model,state,chunk", ROWS_WRITES)
+def test_bf16_write_without_token_edges(d_ff, d_model, state, chunk):
+    wl = small_workload(d_ff, d_model, "bf16", state, 3)
+    say("bf16 write edge", d_ff, d_model, state, chunk)
+    src = TensorSource(wl)
+    sess = Session(wl, src)
+    group = [2, 0]
+    ev = [evidence(wl, chunk, r) for r in group]
+    guard = sess.slots[1][0][1].fill_(7.0)                   # an owner outside the group
+    st = write_group(sess, group, 0, chunk, [to_device(z, "bf16") for z, _ in ev],
+                     [to_device(g, "bf16") for _, g in ev])
+    assert st == R.RWTTT_OK
+    torch.cuda.synchronize()
+    for r, (Z, G) in zip(group, ev):
+        D = O.widen(src.dw_init(r, 0), state)
+        want = O.write_candidate(D, O.widen(Z, "bf16"), O.widen(G, "bf16"), wl.eta)
+        assert rel_norm(host_f64(sess.shadow(r, 0), state), want) <= norm_tol(state), r
+    assert torch.all(guard == 7.0)
+
+
+def test_bf16_write_keeps_non_finite_evidence_in_its_place():
+    wl = small_workload(136, 72, "bf16", "f32", 1)
+    sess = Session(wl, TensorSource(wl))
+    Z, G = evidence(wl, 21, 0)
+    zd, gd = to_device(Z, "bf16"), to_device(G, "bf16")
+    zd[20, 135], gd[20, 71] = float("inf"), float("nan")
+    assert write_group(sess, [0], 0, 21, [zd], [gd]) == R.RWTTT_OK
+    bad = ~torch.isfinite(sess.shadow(0, 0))
+    want = torch.zeros_like(bad)
+    want[135, :] = want[:, 71] = True
+    assert torch.equal(bad, want)
