@@ -1128,40 +1128,11 @@ constexpr int kRTM = 64;                 // rows per wave
 constexpr int kRTN = 64;                 // columns per wave
 constexpr int kRMaxC = 384;              // largest chunk on this path
 
-template <bool NT>
-__global__ void __launch_bounds__(kRThreads) __attribute__((amdgpu_waves_per_eu(3, 3)))
-write_rows_kernel(const WriteParams p) {
+// The product of a wave's 64 rows and 64 columns over the whole chunk: zoff and
+// goff are the lane's byte offsets in a row of Z and of G.
+__device__ __forceinline__ void rows_product(const WriteParams& p, const uint16_t* Z, const uint16_t* G,
+                                             uint32_t zoff, uint32_t goff, int q4, f32x4_t (&acc)[4][4]) {
   constexpr int RS = 16;                 // evidence rows per matrix step
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-  const int i16 = lane & 15, q4 = lane >> 4;
-  const int b = blockIdx.y;
-  // blocks are dealt to the XCDs round-robin: each round of eight is rotated by
-  // one, or a power of two of columns would give an XCD always the same ones
-  // (30.4 against 24.2 us for two owners of 8192 x 1024)
-  const int bx = (int(blockIdx.x) & ~7) | ((int(blockIdx.x) + (int(blockIdx.x) >> 3)) & 7);
-  const int tile = bx * (kRThreads / 64) + wave;         // the waves are independent
-  const int mt = tile / p.ntl;
-  if (mt >= p.mt) return;
-  const int m0 = mt * kRTM + 16 * q4;                    // this lane's 16 rows: two runs of eight, each
-                                                         // inside or outside the matrix as a whole
-  const int n0 = (tile - mt * p.ntl) * kRTN + 4 * i16;
-  const bool n_ok = n0 < p.d_model;
-  const int n = min(n0, p.d_model - 4);                  // ... and four columns
-  const uint16_t* Z = static_cast<const uint16_t*>(p.z[b]);
-  const uint16_t* G = static_cast<const uint16_t*>(p.g[b]);
-
-  // the live rows are requested first: row r is register r / 4 of matrix r % 4
-  Packed<float, 4> lv[16];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const float* live = static_cast<const float*>(p.live[b]) + size_t(min(m0 + 8 * h, p.d_ff - 8)) * p.d_model + n;
-#pragma unroll
-    for (int r = 0; r < 8; ++r) load_packed<NT>(live + size_t(r) * p.d_model, lv[8 * h + r]);
-  }
-
-  const uint32_t zoff = uint32_t(min(mt * kRTM + 4 * i16, p.d_ff - 4)) * 2u, goff = uint32_t(n) * 2u;
-  f32x4_t acc[4][4];
 #pragma unroll
   for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -1202,6 +1173,42 @@ write_rows_kernel(const WriteParams p) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(az[t], bg[u], acc[t][u], 0, 0, 0);
   }
+}
+
+template <bool NT>
+__global__ void __launch_bounds__(kRThreads) __attribute__((amdgpu_waves_per_eu(3, 3)))
+write_rows_kernel(const WriteParams p) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  const int i16 = lane & 15, q4 = lane >> 4;
+  const int b = blockIdx.y;
+  // blocks are dealt to the XCDs round-robin: each round of eight is rotated by
+  // one, or a power of two of columns would give an XCD always the same ones
+  // (30.4 against 24.2 us for two owners of 8192 x 1024)
+  const int bx = (int(blockIdx.x) & ~7) | ((int(blockIdx.x) + (int(blockIdx.x) >> 3)) & 7);
+  const int tile = bx * (kRThreads / 64) + wave;         // the waves are independent
+  const int mt = tile / p.ntl;
+  if (mt >= p.mt) return;
+  const int m0 = mt * kRTM + 16 * q4;                    // this lane's 16 rows: two runs of eight, each
+                                                         // inside or outside the matrix as a whole
+  const int n0 = (tile - mt * p.ntl) * kRTN + 4 * i16;
+  const bool n_ok = n0 < p.d_model;
+  const int n = min(n0, p.d_model - 4);                  // ... and four columns
+  const uint16_t* Z = static_cast<const uint16_t*>(p.z[b]);
+  const uint16_t* G = static_cast<const uint16_t*>(p.g[b]);
+
+  // the live rows are requested first: row r is register r / 4 of matrix r % 4
+  Packed<float, 4> lv[16];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const float* live = static_cast<const float*>(p.live[b]) + size_t(min(m0 + 8 * h, p.d_ff - 8)) * p.d_model + n;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) load_packed<NT>(live + size_t(r) * p.d_model, lv[8 * h + r]);
+  }
+
+  const uint32_t zoff = uint32_t(min(mt * kRTM + 4 * i16, p.d_ff - 4)) * 2u, goff = uint32_t(n) * 2u;
+  f32x4_t acc[4][4];
+  rows_product(p, Z, G, zoff, goff, q4, acc);
 
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
@@ -1211,6 +1218,94 @@ write_rows_kernel(const WriteParams p) {
     if (n_ok && m0 + (r & 8) < p.d_ff)
       store_n<4, true>(static_cast<float*>(p.shadow[b]) + size_t(m0 + r) * p.d_model + n, o);
   }
+}
+
+// With a fused token (C <= 64) the waves also load W0's rows, and two blocks fit
+// a CU.  A block is four waves side by side and leaves one token partial per
+// (owner, 64 rows) in the region of the streaming kernel, whose 64 rows per owner
+// end at 4096 matrix rows.  Against the streaming kernel, whose blocks start with a
+// G tile staged through LDS and have few items on a small state, in us: 1000 x
+// 4000, C = 20, two owners 15.9 / 19.8, C = 64, eight 59.8 / 72.8; 2496 x 824 x 1,
+// C = 64, 11.9 / 12.9; 2000 x 2000 x 6, C = 20, 48.1 / 54.9; 4096 x 1024, C = 16, three
+// 26.0 / 27.4, C = 64, eight 59.6 / 60.1.  Outside the rule: few columns are
+// padded to 256 (45.9 / 44.7 at 3000 x 296 x 16, C = 64); blocks two waves wide, for
+// more rows, win with few owners (26.7 / 31.2 at 6000 x 600 x 3) and lose with many
+// (69.6 / 64.3 with eight, 106.0 / 91.8 at 8000 x 1000 x 6), and one wave wide
+// lose (137.5 / 118.7 at 14000 x 1400 x 3); bf16 state has half the bytes for the
+// same evidence loads (36.8 / 34.5 at 9728 x 2560).  The rule looks at the matrix
+// alone, so that an owner's token has the same bits in any group.
+constexpr size_t kRTokenElems = size_t(4) << 20;
+
+bool rows_token(int d_ff, int d_model) {
+  return d_ff <= kRTM * kSParts && d_model >= 512 && size_t(d_ff) * d_model <= kRTokenElems;
+}
+
+template <bool NT>
+__global__ void __launch_bounds__(kRThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+write_rows_token_kernel(const WriteParams p) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  const int i16 = lane & 15, q4 = lane >> 4;
+  // block -> (XCD, position) -> ((rows, columns) pair, slot): the slots of one
+  // pair sit on one XCD, so that W0 comes from HBM once.  Rounds of eight are
+  // rotated as above
+  const int xcd = blockIdx.x & 7;
+  const int pos = blockIdx.x >> 3;
+  const int pl = pos / p.count;
+  const int b = pos - pl * p.count;
+  const int pair = pl * 8 + ((xcd + pl) & 7);
+  if (pair >= p.mt * p.ntl) return;
+  const int mt = pair / p.ntl;
+  const int mw = mt * kRTM;                              // the block's first row
+  const int n0 = ((pair - mt * p.ntl) * (kRThreads / 64) + wave) * kRTN + 4 * i16;
+  const int m0 = mw + 16 * q4;                           // this lane's 16 rows
+  const bool n_ok = n0 < p.d_model;
+  const int n = min(n0, p.d_model - 4);                  // ... and four columns
+  const uint16_t* X = static_cast<const uint16_t*>(p.x) + size_t(p.row[b]) * p.d_ff;
+  Packed<float, 4> lv[16];
+  Packed<uint16_t, 4> wv[16];
+  Packed<uint16_t, 8> xv[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int m = min(m0 + 8 * h, p.d_ff - 8);
+    const size_t at = size_t(m) * p.d_model + n;
+    load_packed<false>(X + m, xv[h]);
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      load_packed<NT>(static_cast<const float*>(p.live[b]) + at + size_t(r) * p.d_model, lv[8 * h + r]);
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      load_packed<false>(static_cast<const uint16_t*>(p.w0) + at + size_t(r) * p.d_model, wv[8 * h + r]);
+  }
+  float y[4] = {0.f, 0.f, 0.f, 0.f};
+  f32x4_t acc[4][4];
+  rows_product(p, static_cast<const uint16_t*>(p.z[b]), static_cast<const uint16_t*>(p.g[b]),
+               uint32_t(min(mw + 4 * i16, p.d_ff - 4)) * 2u, uint32_t(n) * 2u, q4, acc);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    float o[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) o[u] = lv[r].get(u) + p.eta * acc[r & 3][u][r >> 2];
+    if (n_ok && m0 + (r & 8) < p.d_ff)
+      store_n<4, true>(static_cast<float*>(p.shadow[b]) + size_t(m0 + r) * p.d_model + n, o);
+  }
+  // token: x live + x W0 over this lane's rows, in row order
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const float x = xv[r >> 3].get(r & 7);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float t = fmaf(x, wv[r].get(u), fmaf(x, lv[r].get(u), y[u]));
+      y[u] = m0 + (r & 8) < p.d_ff ? t : y[u];           // rows past the matrix are copies
+    }
+  }
+  // the four quarters' rows as a tree
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    y[u] += __shfl_xor(y[u], 16);
+    y[u] += __shfl_xor(y[u], 32);
+  }
+  if (q4 == 0 && n_ok) store_n<4>(p.tpart + (size_t(p.row[b]) * p.parts + mt) * p.npadw + n0, y);
 }
 
 // ---------------------------------------------------------------------------
@@ -1387,6 +1482,20 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
     };
     if (cached) by_rows(std::false_type{});
     else by_rows(std::true_type{});
+    return hipGetLastError();
+  }
+  if (!L.state_bf16 && token && L.chunk <= kSMaxC && rows_token(L.d_ff, L.d_model)) {
+    constexpr int tile = kRThreads / 64 * kRTN;
+    p.mt = p.parts = (L.d_ff + kRTM - 1) / kRTM;
+    p.ntl = (L.d_model + tile - 1) / tile;
+    p.npadw = geo.tnpad;
+    p.tpart = reinterpret_cast<float*>(static_cast<char*>(L.workspace) + geo.token_offset);
+    const dim3 grid(unsigned((p.mt * p.ntl + 7) / 8 * 8) * unsigned(L.count));
+    if (cached)
+      hipLaunchKernelGGL((write_rows_token_kernel<false>), grid, dim3(kRThreads), 0, stream, p);
+    else
+      hipLaunchKernelGGL((write_rows_token_kernel<true>), grid, dim3(kRThreads), 0, stream, p);
+    reduce_token();
     return hipGetLastError();
   }
   if (L.chunk <= kSMaxC && token) {

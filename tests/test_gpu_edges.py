@@ -211,3 +211,43 @@ def test_bf16_write_keeps_non_finite_evidence_in_its_place():
     want = torch.zeros_like(bad)
     want[135, :] = want[:, 71] = True
     assert torch.equal(bad, want)
+
+
+# the routes of a bf16 WRITE with a fused token and fp32 state: register operands
+# from 512 columns, up to 4096 rows and 4 M elements, streaming outside
+TOKEN_WRITES = [
+    (8, 512, 1), (72, 520, 16), (264, 776, 17), (1032, 520, 64), (4096, 512, 33), (4096, 1024, 31),
+    (8, 8, 1), (264, 504, 17), (4104, 512, 33), (4096, 1032, 31),
+]
+
+
+@pytest.mark.parametrize("d_ff,d_model,chunk", TOKEN_WRITES)
+def test_bf16_write_with_token_edges(d_ff, d_model, chunk):
+    """Token and candidate of two owners (slots in reverse owner order) against
+    64 bits, and the bits of an owner alone."""
+    say("token write", d_ff, d_model, chunk)
+    wl = small_workload(d_ff, d_model, "bf16", "f32", 3, eta=0.01)
+    src = TensorSource(wl)
+    sess = Session(wl, src)
+    x = draw((3, d_ff), 1.0, "bf16", wl.seed, (61,))
+    xd = to_device(x, "bf16")
+    group = [2, 0]
+    zs, gs = zip(*(evidence(wl, chunk, r) for r in group))
+    zd, gd = [to_device(z, "bf16") for z in zs], [to_device(g, "bf16") for g in gs]
+    y = torch.full((3, d_model), float("nan"), dtype=torch.bfloat16, device="cuda")
+    assert write_group(sess, group, 0, chunk, zd, gd, x_dev=xd, y_dev=y) == R.RWTTT_OK
+    assert R.rwttt_rollback(sess.ctx, group) == R.RWTTT_OK
+    torch.cuda.synchronize()
+    both = [sess.shadow(r, 0).clone() for r in group]
+    w0 = O.widen(src.w0(0), "bf16")
+    for i, r in enumerate(group):
+        live = O.widen(src.dw_init(r, 0), "f32")
+        assert rel_norm(host_f64(y[r], "bf16"), O.read_apply(O.widen(x[r], "bf16"), w0, live)) <= norm_tol("bf16"), r
+        want = O.write_candidate(live, O.widen(zs[i], "bf16"), O.widen(gs[i], "bf16"), wl.eta)
+        assert rel_norm(host_f64(both[i], "f32"), want) <= norm_tol("f32"), r
+        alone = torch.zeros_like(y)
+        assert write_group(sess, [r], 0, chunk, [zd[i]], [gd[i]], x_dev=xd, y_dev=alone) == R.RWTTT_OK
+        assert R.rwttt_rollback(sess.ctx, [r]) == R.RWTTT_OK
+        torch.cuda.synchronize()
+        assert torch.equal(alone[r], y[r]) and torch.equal(sess.shadow(r, 0), both[i])
+    assert torch.isnan(y[1]).all()
