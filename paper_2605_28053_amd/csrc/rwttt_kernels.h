@@ -7,16 +7,9 @@
 #include <stdint.h>
 
 #include "rwttt.h"
+#include "rwttt_routes.h"
 
 namespace rwttt {
-
-// READ tiling.  A work item is (group slot, K chunk, column tile).  The chunk
-// and tile sizes depend only on the matrix shape, never on the group, so an
-// owner's result does not depend on who else is in the group.
-constexpr int kReadChunk = 256;       // K rows per work item
-
-constexpr int read_cols_per_lane(int state_bf16) { return state_bf16 ? 8 : 4; }   // 16 B per lane
-inline int read_tile_n(int state_bf16) { return 64 * read_cols_per_lane(state_bf16); }
 
 struct ReadGeometry {
   int ks;       // K chunks

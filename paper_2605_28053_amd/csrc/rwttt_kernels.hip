@@ -94,21 +94,6 @@ __device__ __forceinline__ void tree_push(float (&stack)[N][COLS], int i, const 
       for (int c = 0; c < COLS; ++c) stack[k][c] = t[c];
 }
 
-// Whether the live state that a call reads is little enough to leave in the 256
-// MB last-level cache for the calls after it: loaded without the non-temporal
-// hint it stays there, several such states beside each other, and a later call
-// finds it.  In us without / with the hint, calls on three states in turn, then
-// on six (so that the last-level cache is too small): READ of four owners of 2048
-// x 2048 bf16 (42 MB) 11.8 / 16.4, 15.4 / 16.5; WRITE of two of 3072 x 1024
-// (25 MB) 9.0 / 10.3, 9.0 / 10.6, of eight of 600 x 2000 (38 MB) 14.8 / 19.7,
-// 18.6 / 20.0.  Above, the states push each other out and the hint is better:
-// READ of one owner of 9728 x 2560 (149 MB) 31.8 / 27.4 us, and a large READ
-// would push W0 out of L2 (eight owners 147 / 128 us).  Stores always have the
-// hint: a candidate kept in the cache takes the place of a live state (one WRITE
-// of 9728 x 2560, C = 64, 54.6 against 48.1 us).  The GEMM keeps it for its live tiles too: its evidence lives
-// in L2 (62.2 against 59.6 us for 11 owners of 5448 x 288 bf16, C = 650).
-inline bool stays_cached(size_t live_bytes) { return live_bytes <= 48000000; }
-
 // Balanced tree over N (a power of two) values in index order.
 template <int N> __device__ __forceinline__ float tree_sum(float (&v)[N]) {
 #pragma unroll
@@ -251,18 +236,10 @@ __global__ void __launch_bounds__(256) read_reduce_kernel(const ReadParams p) {
 // and a second launch: two owners of 256 x 64 fp32 7.4 us (the host's time for
 // the call) against 11.2 before, four of 976 x 1920 8.1 against 16.8.  The same
 // tree over the same leaves of eight rows as the two launches.
-//
-// Where the two launches are better: a block's column of LEAVES leaves reaches
-// only about 70 GB/s, and 128-byte runs 4 TB/s over the chip.  One launch
-// against two, in us: 8.0/11.8 at 1024 x 512 x 4 owners, 8.5/12.2 at 512 x
-// 4096 x 4 (38 MB), 15.9/14.0 at 512 x 4096 x 8 (71 MB), 10.6/12.9 at 1056 x
-// 1008 x 6, 12.5/11.6 at 2048 x 512 x 4.
-constexpr size_t kDirectBytes = 36000000;
 constexpr int kDirectThreads = 1024;
 constexpr int kDirectLanes = 8;
 constexpr int kDirectGroups = kDirectThreads / kDirectLanes;
 constexpr int kDirectLeaf = kUnroll;
-constexpr int kDirectRows = 1536;          // at most two leaves per group
 static_assert(kDirectRows <= 2 * kDirectGroups * kDirectLeaf && kDirectRows <= kTreeChunks * kReadChunk, "");
 
 template <typename IO, typename ST, int LEAVES>
@@ -377,24 +354,7 @@ struct WriteParams {
 // HBM once.  The partition of an owner's rows never depends on the group, so
 // an owner's token and candidate are bit-identical in any group.
 
-constexpr int kSTM = 32;                 // rows per item
-constexpr int kSTN = 256;                // columns per tile
-constexpr int kSMaxC = 64;               // largest chunk on this path
 constexpr int kSPitch = kSMaxC + 8;      // bf16 per staged rank row (144 B: 16 rows hit 16 bank groups)
-constexpr int kSParts = 64;              // most row-tile partitions per (owner, column tile)
-constexpr int kSSlots = 512;             // blocks of this kernel resident at once (256 CUs x 2)
-
-// Row-tile partitions per (owner, column tile), from the shape alone, so that
-// an owner's token partials are added in the same order in any group: as many
-// as let one owner's blocks fill one round of the block slots, then the fewest
-// that keep the largest partition at the same number of items.
-int stream_parts(int d_ff, int d_model) {
-  const int mt = (d_ff + kSTM - 1) / kSTM;
-  const int ntl = (d_model + kSTN - 1) / kSTN;
-  const int pmax = std::max(1, std::min(std::min(kSParts, mt), kSSlots / ntl));
-  const int items = (mt + pmax - 1) / pmax;
-  return (mt + items - 1) / items;
-}
 
 // Rows m0 + 8 wave .. + 7 of a [d_ff, d_model] matrix, 4 columns at ncol.  The
 // live state is read once (non-temporal); W0 is read by every slot of the
@@ -601,8 +561,6 @@ write_stream_kernel(const WriteParams p) {
 // into the freed stages; fp32 state: a register epilogue through a private LDS region) and
 // stores whole rows, rounding to bf16 with the hardware packed convert.
 
-constexpr int kGTM = 256;                                 // rows (d_ff) per tile
-constexpr int kGTN = 128;                                 // columns (d_model) per tile
 constexpr int kGKC = 32;                                  // ranks per LDS stage
 constexpr int kGThreads = 256;                            // 4 waves of 64 x 128
 constexpr int kGStageA = kGKC * kGTM;                     // bf16 elements of Z per stage
@@ -610,8 +568,6 @@ constexpr int kGStage = kGStageA + kGKC * kGTN;           // 24 KB per stage
 constexpr int kGUnitsA = kGStageA * 2 / 1024;             // 1 KB copies of Z per stage (16)
 constexpr int kGUnits = kGStage * 2 / 1024;               // 1 KB copies per stage (24)
 constexpr int kGCopies = kGUnits / 4;                     // copies per wave per stage (6)
-constexpr int kGColGroups = 2;                            // column-tile groups over the XCDs
-constexpr int kGRowClasses = 8 / kGColGroups;             // row-tile classes over the XCDs
 
 typedef short i16x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
@@ -687,20 +643,8 @@ write_gemm_kernel(const WriteParams p) {
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  // block -> (owner, row tile, column tile).  Blocks are dealt to the 8
-  // XCDs round-robin; XCD x takes column-tile half x % 2 and the row tiles
-  // congruent to x / 2 mod 4, so each Z row tile is read by two XCDs and each
-  // G column tile by four.  Consecutive blocks of an XCD share their Z row
-  // tile, and the XCD's G columns (2 MB at C = 512) stay in its L2 while the
-  // live state streams past them non-temporally.
-  const int xcd = blockIdx.x & 7;
-  const int pos = blockIdx.x >> 3;
-  const int ntg = (p.ntl + kGColGroups - 1) / kGColGroups;
-  const int mtq = (p.mt + kGRowClasses - 1) / kGRowClasses;
-  const int nt = (xcd % kGColGroups) * ntg + pos % ntg;
-  const int rest = pos / ntg;
-  const int b = rest / mtq;
-  const int mt = (rest - b * mtq) * kGRowClasses + xcd / kGColGroups;
+  const GemmTile tile = gemm_tile(blockIdx.x, p.mt, p.ntl);
+  const int b = tile.b, mt = tile.mt, nt = tile.nt;
   if (nt >= p.ntl || mt >= p.mt || b >= p.count) return;
   const int m0 = mt * kGTM;
   const int n0 = nt * kGTN;
@@ -1124,9 +1068,7 @@ write_f32_kernel(const WriteParams p) {
 // 9728 x 2560, C = 32: 71 / 83 us).
 
 constexpr int kRThreads = 256;           // 4 waves, neighbours in a row of tiles
-constexpr int kRTM = 64;                 // rows per wave
 constexpr int kRTN = 64;                 // columns per wave
-constexpr int kRMaxC = 384;              // largest chunk on this path
 
 // The product of a wave's 64 rows and 64 columns over the whole chunk: zoff and
 // goff are the lane's byte offsets in a row of Z and of G.
@@ -1223,23 +1165,7 @@ write_rows_kernel(const WriteParams p) {
 // With a fused token (C <= 64) the waves also load W0's rows, and two blocks fit
 // a CU.  A block is four waves side by side and leaves one token partial per
 // (owner, 64 rows) in the region of the streaming kernel, whose 64 rows per owner
-// end at 4096 matrix rows.  Against the streaming kernel, whose blocks start with a
-// G tile staged through LDS and have few items on a small state, in us: 1000 x
-// 4000, C = 20, two owners 15.9 / 19.8, C = 64, eight 59.8 / 72.8; 2496 x 824 x 1,
-// C = 64, 11.9 / 12.9; 2000 x 2000 x 6, C = 20, 48.1 / 54.9; 4096 x 1024, C = 16, three
-// 26.0 / 27.4, C = 64, eight 59.6 / 60.1.  Outside the rule: few columns are
-// padded to 256 (45.9 / 44.7 at 3000 x 296 x 16, C = 64); blocks two waves wide, for
-// more rows, win with few owners (26.7 / 31.2 at 6000 x 600 x 3) and lose with many
-// (69.6 / 64.3 with eight, 106.0 / 91.8 at 8000 x 1000 x 6), and one wave wide
-// lose (137.5 / 118.7 at 14000 x 1400 x 3); bf16 state has half the bytes for the
-// same evidence loads (36.8 / 34.5 at 9728 x 2560).  The rule looks at the matrix
-// alone, so that an owner's token has the same bits in any group.
-constexpr size_t kRTokenElems = size_t(4) << 20;
-
-bool rows_token(int d_ff, int d_model) {
-  return d_ff <= kRTM * kSParts && d_model >= 512 && size_t(d_ff) * d_model <= kRTokenElems;
-}
-
+// end at 4096 matrix rows.
 template <bool NT>
 __global__ void __launch_bounds__(kRThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 write_rows_token_kernel(const WriteParams p) {
@@ -1380,8 +1306,8 @@ hipError_t launch_read_t(const ReadLaunch& L, hipStream_t stream, float* slot_pa
     p.row[b] = b < L.count ? L.row[b] : 0u;
     p.tail[b] = b < L.count ? L.tail[b] : nullptr;
   }
-  const size_t bytes = size_t(L.d_ff) * L.d_model * (L.count * sizeof(ST) + sizeof(IO));
-  if (L.d_ff <= kDirectRows && bytes <= kDirectBytes) {
+  const ReadRoute route = read_route(sizeof(IO) == 2, sizeof(ST) == 2, L.d_ff, L.d_model, L.count);
+  if (route.direct) {
     constexpr int tile = kDirectLanes * read_cols_per_lane(sizeof(ST) == 2);
     p.nt = (L.d_model + tile - 1) / tile;
     const dim3 grid(unsigned((p.nt + 7) / 8 * 8 * L.count));
@@ -1393,20 +1319,17 @@ hipError_t launch_read_t(const ReadLaunch& L, hipStream_t stream, float* slot_pa
   }
   // (chunk, tile) pairs rounded up to a multiple of the 8 XCDs
   const dim3 grid(unsigned((g.ks * g.nt + 7) / 8 * 8) * unsigned(L.count));
-  // leaves of eight rows where the one launch above must match, and for fp32 io
-  // with bf16 state, where they are faster (20.0 against 23.4 us for two owners
-  // of 3600 x 1512)
   auto run = [&](auto nt) {
     constexpr bool NT = decltype(nt)::value;
-    if (L.d_ff <= kDirectRows || sizeof(IO) > sizeof(ST))
+    if (route.leaf == kDirectLeaf)
       hipLaunchKernelGGL((read_partial_kernel<IO, ST, 8, kDirectLeaf, NT>), grid, dim3(512), 0, stream, p);
-    else if (L.count == 1)
+    else if (route.waves == 4)
       hipLaunchKernelGGL((read_partial_kernel<IO, ST, 4, 32, NT>), grid, dim3(256), 0, stream, p);
     else
       hipLaunchKernelGGL((read_partial_kernel<IO, ST, 8, 32, NT>), grid, dim3(512), 0, stream, p);
   };
-  if (stays_cached(bytes)) run(std::false_type{});
-  else run(std::true_type{});
+  if (route.nt) run(std::true_type{});
+  else run(std::false_type{});
   launch_reduce<IO>(p, L.d_ff <= kDirectRows, stream);
   return hipGetLastError();
 }
@@ -1433,7 +1356,7 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
     p.row[b] = in ? L.row[b] : 0u;
   }
   const bool token = L.x != nullptr;
-  const bool cached = stays_cached(size_t(L.d_ff) * L.d_model * L.count * sizeof(ST));
+  const WriteRoute route = write_route(L.io_bf16, sizeof(ST) == 2, L.d_ff, L.d_model, L.count, L.chunk, token);
   const ReadGeometry geo = read_geometry(L.d_ff, L.d_model, L.state_bf16, L.n_owners);
   // the fused token's partials, p.parts rows of p.npadw per owner
   auto reduce_token = [&] {
@@ -1457,7 +1380,7 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
     if (L.io_bf16) launch_reduce<uint16_t>(q, false, stream);
     else launch_reduce<float>(q, false, stream);
   };
-  if (!L.io_bf16) {
+  if (route.kernel == WriteKernel::f32) {
     auto run = [&](auto wn, auto nt) {
       constexpr int WN = decltype(wn)::value;
       constexpr bool NT = decltype(nt)::value;
@@ -1475,30 +1398,29 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
       }
     };
     auto by_rows = [&](auto nt) {
-      // without a token nothing limits the rows of a block
-      if (!token || L.d_ff * 4 <= kReadChunk * kSParts) run(std::integral_constant<int, 4>{}, nt);
-      else if (L.d_ff * 2 <= kReadChunk * kSParts) run(std::integral_constant<int, 2>{}, nt);
+      if (route.wn == 4) run(std::integral_constant<int, 4>{}, nt);
+      else if (route.wn == 2) run(std::integral_constant<int, 2>{}, nt);
       else run(std::integral_constant<int, 1>{}, nt);
     };
-    if (cached) by_rows(std::false_type{});
-    else by_rows(std::true_type{});
+    if (route.nt) by_rows(std::true_type{});
+    else by_rows(std::false_type{});
     return hipGetLastError();
   }
-  if (!L.state_bf16 && token && L.chunk <= kSMaxC && rows_token(L.d_ff, L.d_model)) {
+  if (route.kernel == WriteKernel::rows_token) {
     constexpr int tile = kRThreads / 64 * kRTN;
     p.mt = p.parts = (L.d_ff + kRTM - 1) / kRTM;
     p.ntl = (L.d_model + tile - 1) / tile;
     p.npadw = geo.tnpad;
     p.tpart = reinterpret_cast<float*>(static_cast<char*>(L.workspace) + geo.token_offset);
     const dim3 grid(unsigned((p.mt * p.ntl + 7) / 8 * 8) * unsigned(L.count));
-    if (cached)
-      hipLaunchKernelGGL((write_rows_token_kernel<false>), grid, dim3(kRThreads), 0, stream, p);
-    else
+    if (route.nt)
       hipLaunchKernelGGL((write_rows_token_kernel<true>), grid, dim3(kRThreads), 0, stream, p);
+    else
+      hipLaunchKernelGGL((write_rows_token_kernel<false>), grid, dim3(kRThreads), 0, stream, p);
     reduce_token();
     return hipGetLastError();
   }
-  if (L.chunk <= kSMaxC && token) {
+  if (route.kernel == WriteKernel::stream) {
     p.mt = (L.d_ff + kSTM - 1) / kSTM;
     p.ntl = (L.d_model + kSTN - 1) / kSTN;
     // partitions of an owner's row tiles: fixed by the shape, never by the group
@@ -1506,14 +1428,14 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
     p.npadw = geo.tnpad;
     p.tpart = reinterpret_cast<float*>(static_cast<char*>(L.workspace) + geo.token_offset);
     const dim3 grid(unsigned((p.ntl * p.parts + 7) / 8 * 8) * unsigned(L.count));
-    if (cached)
-      hipLaunchKernelGGL((write_stream_kernel<ST, false>), grid, dim3(256), 0, stream, p);
-    else
+    if (route.nt)
       hipLaunchKernelGGL((write_stream_kernel<ST, true>), grid, dim3(256), 0, stream, p);
+    else
+      hipLaunchKernelGGL((write_stream_kernel<ST, false>), grid, dim3(256), 0, stream, p);
     reduce_token();
     return hipGetLastError();
   }
-  if (token) {
+  if (route.read_first) {
     // no fused kernel on this path: the token is an ordinary READ of the group at version v
     ReadLaunch R;
     R.io_bf16 = L.io_bf16;
@@ -1534,22 +1456,20 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
     const hipError_t e = launch_read_t<uint16_t, ST>(R, stream);
     if (e != hipSuccess) return e;
   }
-  if (!L.state_bf16 && L.chunk <= kRMaxC) {
+  if (route.kernel == WriteKernel::rows) {
     p.mt = (L.d_ff + kRTM - 1) / kRTM;
     p.ntl = (L.d_model + kRTN - 1) / kRTN;
     constexpr int waves = kRThreads / 64;
     const dim3 grid(unsigned((p.mt * p.ntl + waves - 1) / waves + 7) / 8 * 8, unsigned(L.count));
-    if (cached)
-      hipLaunchKernelGGL((write_rows_kernel<false>), grid, dim3(kRThreads), 0, stream, p);
-    else
+    if (route.nt)
       hipLaunchKernelGGL((write_rows_kernel<true>), grid, dim3(kRThreads), 0, stream, p);
+    else
+      hipLaunchKernelGGL((write_rows_kernel<false>), grid, dim3(kRThreads), 0, stream, p);
     return hipGetLastError();
   }
   p.mt = (L.d_ff + kGTM - 1) / kGTM;
   p.ntl = (L.d_model + kGTN - 1) / kGTN;
-  const unsigned ntg = unsigned((p.ntl + kGColGroups - 1) / kGColGroups);
-  const unsigned mtq = unsigned((p.mt + kGRowClasses - 1) / kGRowClasses);
-  const dim3 grid(unsigned(L.count) * mtq * ntg * 8u);
+  const dim3 grid(gemm_blocks(L.count, p.mt, p.ntl));
   hipLaunchKernelGGL((write_gemm_kernel<ST>), grid, dim3(kGThreads), 0, stream, p);
   return hipGetLastError();
 }

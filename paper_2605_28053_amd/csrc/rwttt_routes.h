@@ -1,0 +1,168 @@
+// Which kernel a call takes, as functions of sizes and types alone: host C++
+// without HIP, so that the rules can be checked on any machine.  Kernels that
+// share a call's range add in the same order, so a rule may look at the group's
+// size without changing an owner's bits.
+#pragma once
+
+#include <stddef.h>
+
+#include <algorithm>
+
+namespace rwttt {
+
+// READ tiling.  A work item is (group slot, K chunk, column tile).  The chunk
+// and tile sizes depend only on the matrix shape, never on the group, so an
+// owner's result does not depend on who else is in the group.
+constexpr int kReadChunk = 256;       // K rows per work item
+
+constexpr int read_cols_per_lane(int state_bf16) { return state_bf16 ? 8 : 4; }   // 16 B per lane
+constexpr int read_tile_n(int state_bf16) { return 64 * read_cols_per_lane(state_bf16); }
+
+// Whether the live state that a call reads is little enough to leave in the 256
+// MB last-level cache for the calls after it: loaded without the non-temporal
+// hint it stays there, several such states beside each other, and a later call
+// finds it.  In us without / with the hint, calls on three states in turn, then
+// on six (so that the last-level cache is too small): READ of four owners of 2048
+// x 2048 bf16 (42 MB) 11.8 / 16.4, 15.4 / 16.5; WRITE of two of 3072 x 1024
+// (25 MB) 9.0 / 10.3, 9.0 / 10.6, of eight of 600 x 2000 (38 MB) 14.8 / 19.7,
+// 18.6 / 20.0.  Above, the states push each other out and the hint is better:
+// READ of one owner of 9728 x 2560 (149 MB) 31.8 / 27.4 us, and a large READ
+// would push W0 out of L2 (eight owners 147 / 128 us).  Stores always have the
+// hint: a candidate kept in the cache takes the place of a live state (one WRITE
+// of 9728 x 2560, C = 64, 54.6 against 48.1 us).  The GEMM keeps it for its live tiles too: its evidence lives
+// in L2 (62.2 against 59.6 us for 11 owners of 5448 x 288 bf16, C = 650).
+inline bool stays_cached(size_t live_bytes) { return live_bytes <= 48000000; }
+
+// ---------------------------------------------------------------------------
+// READ
+// ---------------------------------------------------------------------------
+
+// Where the two launches are better than one (read_direct_kernel): a block's column of LEAVES leaves reaches
+// only about 70 GB/s, and 128-byte runs 4 TB/s over the chip.  One launch
+// against two, in us: 8.0/11.8 at 1024 x 512 x 4 owners, 8.5/12.2 at 512 x
+// 4096 x 4 (38 MB), 15.9/14.0 at 512 x 4096 x 8 (71 MB), 10.6/12.9 at 1056 x
+// 1008 x 6, 12.5/11.6 at 2048 x 512 x 4.
+constexpr size_t kDirectBytes = 36000000;
+constexpr int kDirectRows = 1536;          // at most two leaves per row group
+
+struct ReadRoute {
+  bool direct;               // one launch
+  int waves, leaf;           // two launches: waves of a block, rows of a leaf
+  bool nt;                   // live state loaded with the non-temporal hint
+};
+
+inline ReadRoute read_route(bool io_bf16, bool state_bf16, int d_ff, int d_model, int count) {
+  const size_t io = io_bf16 ? 2 : 4, state = state_bf16 ? 2 : 4;
+  const size_t bytes = size_t(d_ff) * d_model * (count * state + io);
+  ReadRoute r;
+  r.direct = d_ff <= kDirectRows && bytes <= kDirectBytes;
+  r.nt = !stays_cached(bytes);
+  // leaves of eight rows where the one launch above must match, and for fp32 io
+  // with bf16 state, where they are faster (20.0 against 23.4 us for two owners
+  // of 3600 x 1512)
+  r.leaf = d_ff <= kDirectRows || io > state ? 8 : 32;
+  r.waves = r.leaf == 32 && count == 1 ? 4 : 8;
+  return r;
+}
+
+// ---------------------------------------------------------------------------
+// WRITE
+// ---------------------------------------------------------------------------
+
+constexpr int kSTM = 32;                 // streaming kernel: rows per item
+constexpr int kSTN = 256;                // columns per tile
+constexpr int kSMaxC = 64;               // largest chunk on this path
+constexpr int kSParts = 64;              // most row-tile partitions per (owner, column tile)
+constexpr int kSSlots = 512;             // blocks of this kernel resident at once (256 CUs x 2)
+
+// Row-tile partitions per (owner, column tile), from the shape alone, so that
+// an owner's token partials are added in the same order in any group: as many
+// as let one owner's blocks fill one round of the block slots, then the fewest
+// that keep the largest partition at the same number of items.
+inline int stream_parts(int d_ff, int d_model) {
+  const int mt = (d_ff + kSTM - 1) / kSTM;
+  const int ntl = (d_model + kSTN - 1) / kSTN;
+  const int pmax = std::max(1, std::min(std::min(kSParts, mt), kSSlots / ntl));
+  const int items = (mt + pmax - 1) / pmax;
+  return (mt + items - 1) / items;
+}
+
+constexpr int kRTM = 64;                 // register-operand kernels: rows per wave
+constexpr int kRMaxC = 384;              // largest chunk without a fused token on this path
+
+// With a fused token: against the streaming kernel, whose blocks start with a
+// G tile staged through LDS and have few items on a small state, in us: 1000 x
+// 4000, C = 20, two owners 15.9 / 19.8, C = 64, eight 59.8 / 72.8; 2496 x 824 x 1,
+// C = 64, 11.9 / 12.9; 2000 x 2000 x 6, C = 20, 48.1 / 54.9; 4096 x 1024, C = 16, three
+// 26.0 / 27.4, C = 64, eight 59.6 / 60.1.  Outside the rule: few columns are
+// padded to 256 (45.9 / 44.7 at 3000 x 296 x 16, C = 64); blocks two waves wide, for
+// more rows, win with few owners (26.7 / 31.2 at 6000 x 600 x 3) and lose with many
+// (69.6 / 64.3 with eight, 106.0 / 91.8 at 8000 x 1000 x 6), and one wave wide
+// lose (137.5 / 118.7 at 14000 x 1400 x 3); bf16 state has half the bytes for the
+// same evidence loads (36.8 / 34.5 at 9728 x 2560).  The rule looks at the matrix
+// alone: the two kernels add a token's rows in different orders.
+constexpr size_t kRTokenElems = size_t(4) << 20;
+
+inline bool rows_token(int d_ff, int d_model) {
+  return d_ff <= kRTM * kSParts && d_model >= 512 && size_t(d_ff) * d_model <= kRTokenElems;
+}
+
+constexpr int kGTM = 256;                // GEMM: rows (d_ff) per tile
+constexpr int kGTN = 128;                // columns (d_model) per tile
+constexpr int kGColGroups = 2;           // column-tile groups over the XCDs
+constexpr int kGRowClasses = 8 / kGColGroups;             // row-tile classes over the XCDs
+
+struct GemmTile {
+  int b, mt, nt;             // group slot, row tile, column tile; a tile past the end is idle
+};
+
+// Block -> tile.  Blocks are dealt to the 8 XCDs round-robin; XCD x takes
+// column-tile half x % 2 and the row tiles congruent to x / 2 mod 4, so each Z
+// row tile is read by two XCDs and each G column tile by four.  Consecutive
+// blocks of an XCD share their Z row tile, and the XCD's G columns (2 MB at C =
+// 512) stay in its L2 while the live state streams past them non-temporally.
+constexpr GemmTile gemm_tile(unsigned block, int mt, int ntl) {
+  const int xcd = block & 7;
+  const int pos = block >> 3;
+  const int ntg = (ntl + kGColGroups - 1) / kGColGroups;
+  const int mtq = (mt + kGRowClasses - 1) / kGRowClasses;
+  const int rest = pos / ntg;
+  const int b = rest / mtq;
+  return {b, (rest - b * mtq) * kGRowClasses + xcd / kGColGroups, (xcd % kGColGroups) * ntg + pos % ntg};
+}
+
+constexpr unsigned gemm_blocks(int count, int mt, int ntl) {
+  const unsigned ntg = unsigned((ntl + kGColGroups - 1) / kGColGroups);
+  const unsigned mtq = unsigned((mt + kGRowClasses - 1) / kGRowClasses);
+  return unsigned(count) * mtq * ntg * 8u;
+}
+
+enum class WriteKernel { f32, rows_token, stream, rows, gemm };
+
+struct WriteRoute {
+  WriteKernel kernel;
+  bool read_first;           // the token is a READ of the group before the update
+  int wn;                    // f32: waves of a block side by side
+  bool nt;                   // live state loaded with the non-temporal hint
+};
+
+inline WriteRoute write_route(bool io_bf16, bool state_bf16, int d_ff, int d_model, int count, int chunk,
+                              bool token) {
+  WriteRoute r = {WriteKernel::gemm, false, 0, true};
+  r.nt = !stays_cached(size_t(d_ff) * d_model * count * (state_bf16 ? 2 : 4));
+  if (!io_bf16) {
+    r.kernel = WriteKernel::f32;
+    // without a token nothing limits the rows of a block
+    r.wn = !token || d_ff * 4 <= kReadChunk * kSParts ? 4 : d_ff * 2 <= kReadChunk * kSParts ? 2 : 1;
+    return r;
+  }
+  if (token && chunk <= kSMaxC) {
+    r.kernel = !state_bf16 && rows_token(d_ff, d_model) ? WriteKernel::rows_token : WriteKernel::stream;
+    return r;
+  }
+  r.read_first = token;
+  if (!state_bf16 && chunk <= kRMaxC) r.kernel = WriteKernel::rows;
+  return r;
+}
+
+}  // namespace rwttt

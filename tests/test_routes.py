@@ -1,0 +1,61 @@
+"""Which kernel a call takes: the host rules of the library, on the CPU.
+
+A small program over the library's own header answers one query per line.
+"""
+
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+READ_CHUNK, TOKEN_ROWS = 256, 64       # K rows of a READ partial; an owner's token partials at most
+DTYPES = [("bf16", "f32"), ("bf16", "bf16"), ("f32", "f32"), ("f32", "bf16")]
+# the smallest matrix, ragged and power-of-two ones, the full shapes
+SHAPES = [(8, 8), (256, 64), (1000, 264), (256, 4096), (128, 14336), (1024, 1024), (1536, 1032), (1544, 1032),
+          (5000, 128), (4104, 1032), (5000, 1528), (8200, 520), (9728, 2560), (14336, 4096)]
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("routes") / "routes_check")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2605_28053_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "c", "routes_check.cpp"), "-o", exe], check=True)
+
+    def query(*lines):
+        out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True)
+        answers = out.stdout.splitlines()
+        assert len(answers) == len(lines)
+        return [a.split() for a in answers]
+    return query
+
+
+def test_an_owners_order_of_addition_does_not_depend_on_the_group(ask):
+    """READ: the leaves' size.  A bf16 token of C <= 64: the kernel."""
+    for io, state in DTYPES:
+        for d_ff, d_model in SHAPES:
+            counts = (1, 2, 3, 8, 64)
+            reads = ask(*(f"read {io} {state} {d_ff} {d_model} {n}" for n in counts))
+            assert len({leaf for _, _, leaf, _ in reads}) == 1
+            assert all(d_ff <= 1536 and leaf == "8" for direct, _, leaf, _ in reads if direct == "1")
+            tokens = ask(*(f"write {io} {state} {d_ff} {d_model} {n} 40 1" for n in counts))
+            assert len({(kernel, first, wn) for kernel, first, wn, _ in tokens}) == 1
+
+
+def test_token_partials_fit_an_owners_workspace(ask):
+    """Rows of partial sums per owner: 64 of them, or one per READ chunk."""
+    for io, state in DTYPES:
+        for d_ff, d_model in SHAPES:
+            (kernel, _, wn, _), = ask(f"write {io} {state} {d_ff} {d_model} 3 33 1")
+            if kernel == "rows_token":
+                assert -(-d_ff // 64) <= TOKEN_ROWS
+            elif kernel == "f32" and wn != "1":
+                assert -(-d_ff * int(wn) // READ_CHUNK) <= TOKEN_ROWS
+            else:
+                assert kernel == "stream" or wn == "1"
+
+
+def test_gemm_deals_every_tile_once(ask):
+    sizes = [(c, mt, nt) for c in (1, 2, 8) for mt in (1, 2, 3, 4, 5, 20, 56) for nt in (1, 2, 3, 12, 32, 112)]
+    for size, answer in zip(sizes, ask(*(f"gemm {c} {mt} {nt}" for c, mt, nt in sizes))):
+        assert answer[0] == "1", size
