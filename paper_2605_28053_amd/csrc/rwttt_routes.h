@@ -116,12 +116,24 @@ struct GemmTile {
   int b, mt, nt;             // group slot, row tile, column tile; a tile past the end is idle
 };
 
+// Whether the classes below would leave XCDs without a tile: then the tiles are
+// dealt to the XCDs one by one.  In us, by classes / one by one, bf16 state: eight
+// owners of 256 x 4096, C = 16, 18.4 / 8.1, C = 128 22.4 / 9.9; of 128 x 14336,
+// C = 64, 43.8 / 16.6; of 512 x 2048, C = 16, 12.6 / 7.8; of 5000 x 128, C = 16,
+// 9.5 / 6.2.  Where every XCD has work the classes keep evidence in its L2: 30.2 /
+// 31.9 for eight of 2048 x 2048, C = 128; 7.6 / 8.0 for four of 1000 x 264.
+constexpr bool gemm_few_tiles(int mt, int ntl) { return mt < kGRowClasses || ntl < kGColGroups; }
+
 // Block -> tile.  Blocks are dealt to the 8 XCDs round-robin; XCD x takes
 // column-tile half x % 2 and the row tiles congruent to x / 2 mod 4, so each Z
 // row tile is read by two XCDs and each G column tile by four.  Consecutive
 // blocks of an XCD share their Z row tile, and the XCD's G columns (2 MB at C =
 // 512) stay in its L2 while the live state streams past them non-temporally.
 constexpr GemmTile gemm_tile(unsigned block, int mt, int ntl) {
+  if (gemm_few_tiles(mt, ntl)) {
+    const int row = int(block) / ntl;
+    return {row / mt, row % mt, int(block) % ntl};
+  }
   const int xcd = block & 7;
   const int pos = block >> 3;
   const int ntg = (ntl + kGColGroups - 1) / kGColGroups;
@@ -132,6 +144,7 @@ constexpr GemmTile gemm_tile(unsigned block, int mt, int ntl) {
 }
 
 constexpr unsigned gemm_blocks(int count, int mt, int ntl) {
+  if (gemm_few_tiles(mt, ntl)) return unsigned(count) * unsigned(mt) * unsigned(ntl);
   const unsigned ntg = unsigned((ntl + kGColGroups - 1) / kGColGroups);
   const unsigned mtq = unsigned((mt + kGRowClasses - 1) / kGRowClasses);
   return unsigned(count) * mtq * ntg * 8u;

@@ -59,3 +59,14 @@ def test_gemm_deals_every_tile_once(ask):
     sizes = [(c, mt, nt) for c in (1, 2, 8) for mt in (1, 2, 3, 4, 5, 20, 56) for nt in (1, 2, 3, 12, 32, 112)]
     for size, answer in zip(sizes, ask(*(f"gemm {c} {mt} {nt}" for c, mt, nt in sizes))):
         assert answer[0] == "1", size
+
+
+# below four row tiles or two column tiles of 256 x 128, the smallest that fill
+# the XCDs, and one past a multiple of eight tiles
+@pytest.mark.parametrize("count,d_ff,d_model", [(8, 256, 4096), (8, 128, 14336), (4, 512, 2048), (8, 768, 768),
+                                                (4, 5000, 128), (8, 8192, 64), (1, 256, 1024), (1, 768, 384)])
+def test_few_gemm_tiles_reach_every_xcd(ask, count, d_ff, d_model):
+    mt, nt = -(-d_ff // 256), -(-d_model // 128)
+    (once, *xcds), = ask(f"gemm {count} {mt} {nt}")
+    assert once == "1"
+    assert max(map(int, xcds)) - min(map(int, xcds)) <= 1
