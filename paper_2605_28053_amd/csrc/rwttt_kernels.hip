@@ -329,7 +329,7 @@ struct WriteParams {
 };
 
 // ---------------------------------------------------------------------------
-// WRITE with a token, bf16 evidence, small chunk (C <= 64): streaming rank-C update
+// WRITE, bf16 evidence, small chunk (C <= 64): streaming rank-C update
 // ---------------------------------------------------------------------------
 //
 // For C <= 64 the update moves 2 x |dW| bytes for only 2C flop per element,
@@ -397,7 +397,7 @@ __device__ __forceinline__ void stream_store_pair(uint16_t* dst, int tid, int ro
   }
 }
 
-template <typename ST, bool NT>
+template <typename ST, bool TOKEN, bool NT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 write_stream_kernel(const WriteParams p) {
   constexpr int RPW = kSTM / 4;           // epilogue rows per wave
@@ -448,9 +448,11 @@ write_stream_kernel(const WriteParams p) {
   uint4 za, zb, xq = make_uint4(0, 0, 0, 0);
   stream_load_rows<NT>(live, p.d_ff, p.d_model, part * kSTM, wave, ncol, ncol_ok, lv);
   stream_load_pair(Z, p.d_ff, p.d_ff, p.chunk, part * kSTM, tid, za, zb);
-  stream_load_rows<false>(W0, p.d_ff, p.d_model, part * kSTM, wave, ncol, ncol_ok, wv);
-  if (part * kSTM + wave * RPW < p.d_ff)
-    xq = *reinterpret_cast<const uint4*>(X + part * kSTM + wave * RPW);
+  if constexpr (TOKEN) {
+    stream_load_rows<false>(W0, p.d_ff, p.d_model, part * kSTM, wave, ncol, ncol_ok, wv);
+    if (part * kSTM + wave * RPW < p.d_ff)
+      xq = *reinterpret_cast<const uint4*>(X + part * kSTM + wave * RPW);
+  }
 #pragma unroll
   for (int j = 0; j < kSTN / 32; ++j) stream_store_pair(gt, tid, j * 32, ga[j], gb[j]);
 
@@ -466,9 +468,11 @@ write_stream_kernel(const WriteParams p) {
     if (mn < p.mt) {
       stream_load_rows<NT>(live, p.d_ff, p.d_model, mn * kSTM, wave, ncol, ncol_ok, nx);
       stream_load_pair(Z, p.d_ff, p.d_ff, p.chunk, mn * kSTM, tid, za, zb);
-      stream_load_rows<false>(W0, p.d_ff, p.d_model, mn * kSTM, wave, ncol, ncol_ok, nw);
-      if (mn * kSTM + wave * RPW < p.d_ff)
-        nxq = *reinterpret_cast<const uint4*>(X + mn * kSTM + wave * RPW);
+      if constexpr (TOKEN) {
+        stream_load_rows<false>(W0, p.d_ff, p.d_model, mn * kSTM, wave, ncol, ncol_ok, nw);
+        if (mn * kSTM + wave * RPW < p.d_ff)
+          nxq = *reinterpret_cast<const uint4*>(X + mn * kSTM + wave * RPW);
+      }
     }
     f32x16_t acc[2] = {f32x16_t{}, f32x16_t{}};
 #pragma unroll
@@ -502,31 +506,35 @@ write_stream_kernel(const WriteParams p) {
         store_n<4, true>(shadow + size_t(m) * p.d_model + ncol, o);
       }
     }
-    // token: x[m] * live[m] + x[m] * W0[m] over this wave's rows, in row order
-    const uint32_t xw[4] = {xq.x, xq.y, xq.z, xq.w};
+    if constexpr (TOKEN) {
+      // token: x[m] * live[m] + x[m] * W0[m] over this wave's rows, in row order
+      const uint32_t xw[4] = {xq.x, xq.y, xq.z, xq.w};
 #pragma unroll
-    for (int rr = 0; rr < RPW; ++rr) {
-      const float xv = (rr & 1) ? bf16_hi(xw[rr >> 1]) : bf16_lo(xw[rr >> 1]);
+      for (int rr = 0; rr < RPW; ++rr) {
+        const float xv = (rr & 1) ? bf16_hi(xw[rr >> 1]) : bf16_lo(xw[rr >> 1]);
 #pragma unroll
-      for (int c = 0; c < 4; ++c) yacc[c] = fmaf(xv, wv[rr].get(c), fmaf(xv, lv[rr].get(c), yacc[c]));
+        for (int c = 0; c < 4; ++c) yacc[c] = fmaf(xv, wv[rr].get(c), fmaf(xv, lv[rr].get(c), yacc[c]));
+      }
     }
     if (mn < p.mt) {
 #pragma unroll
       for (int rr = 0; rr < RPW; ++rr) {
         lv[rr] = nx[rr];
-        wv[rr] = nw[rr];
+        if constexpr (TOKEN) wv[rr] = nw[rr];
       }
       xq = nxq;
     }
     __syncthreads();
   }
 
-  // the four waves' token sums in wave order -> one partial per (owner, partition)
+  if constexpr (TOKEN) {
+    // the four waves' token sums in wave order -> one partial per (owner, partition)
 #pragma unroll
-  for (int c = 0; c < 4; ++c) out[wave * kSTN + lane * 4 + c] = yacc[c];
-  __syncthreads();
-  const float v = ((out[tid] + out[kSTN + tid]) + out[2 * kSTN + tid]) + out[3 * kSTN + tid];
-  p.tpart[(size_t(p.row[b]) * p.parts + part) * p.npadw + n0 + tid] = v;
+    for (int c = 0; c < 4; ++c) out[wave * kSTN + lane * 4 + c] = yacc[c];
+    __syncthreads();
+    const float v = ((out[tid] + out[kSTN + tid]) + out[2 * kSTN + tid]) + out[3 * kSTN + tid];
+    p.tpart[(size_t(p.row[b]) * p.parts + part) * p.npadw + n0 + tid] = v;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1063,9 +1071,7 @@ write_f32_kernel(const WriteParams p) {
 // owner of 2496 x 824, C = 159: 8.7 / 15.4.  Half as many state rows per wave
 // needs nearly twice the loads per product (108, 125, 167 at 64, 128, 256).
 // With bf16 state, half the bytes, the GEMM is as fast at C = 16 (78 / 80 us
-// for two owners of 14336 x 4096) and faster above (94 / 82 at C = 64); it also
-// takes the bf16 chunks up to 64 that the streaming kernel had (four owners of
-// 9728 x 2560, C = 32: 71 / 83 us).
+// for two owners of 14336 x 4096) and faster above (94 / 82 at C = 64).
 
 constexpr int kRThreads = 256;           // 4 waves, neighbours in a row of tiles
 constexpr int kRTN = 64;                 // columns per wave
@@ -1426,13 +1432,19 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
     // partitions of an owner's row tiles: fixed by the shape, never by the group
     p.parts = std::min(stream_parts(L.d_ff, L.d_model), geo.tparts);
     p.npadw = geo.tnpad;
-    p.tpart = reinterpret_cast<float*>(static_cast<char*>(L.workspace) + geo.token_offset);
     const dim3 grid(unsigned((p.ntl * p.parts + 7) / 8 * 8) * unsigned(L.count));
-    if (route.nt)
-      hipLaunchKernelGGL((write_stream_kernel<ST, true>), grid, dim3(256), 0, stream, p);
-    else
-      hipLaunchKernelGGL((write_stream_kernel<ST, false>), grid, dim3(256), 0, stream, p);
-    reduce_token();
+    auto run = [&](auto nt) {
+      constexpr bool NT = decltype(nt)::value;
+      if (token) {
+        p.tpart = reinterpret_cast<float*>(static_cast<char*>(L.workspace) + geo.token_offset);
+        hipLaunchKernelGGL((write_stream_kernel<ST, true, NT>), grid, dim3(256), 0, stream, p);
+        reduce_token();
+      } else if constexpr (sizeof(ST) == 2) {
+        hipLaunchKernelGGL((write_stream_kernel<ST, false, NT>), grid, dim3(256), 0, stream, p);
+      }
+    };
+    if (route.nt) run(std::true_type{});
+    else run(std::false_type{});
     return hipGetLastError();
   }
   if (route.read_first) {

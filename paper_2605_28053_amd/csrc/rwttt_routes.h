@@ -87,6 +87,27 @@ inline int stream_parts(int d_ff, int d_model) {
   return (mt + items - 1) / items;
 }
 
+// bf16 state and no token: whether the streaming kernel takes the call rather
+// than the GEMM, whose 256 x 128 tiles are the better split from one round of
+// its 512 block slots up (four owners of 9728 x 2560, C = 32: 83 / 71 us).
+// Streaming / GEMM, in us:
+// * up to a block of one item a CU the streaming kernel's first rows arrive
+//   sooner: 4.5 / 5.6 at 264 x 136, 4.8 / 5.7 at 1000 x 264 x 2, 5.0 / 5.6 at 1024
+//   x 1024 x 2, all C = 1; 5.4 / 5.9 at 2048 x 512, C = 64.  Past it 7.5 / 6.4 at
+//   512 x 2048 x 4, C = 64, and 7.7 / 5.4 at 5000 x 128 (three items a block);
+// * one round of blocks that fills the slots, state from HBM and one stage of
+//   evidence: 21.2 / 22.2 at 9728 x 2560, 43.4 / 45.1 at 14336 x 4096, C = 16 (the
+//   latter 46.4 / 46.0 at C = 48); rows that are no whole 128-byte lines cost the
+//   GEMM's narrower tiles more, at every C: 21.0 / 23.8 at 10000 x 2000.
+constexpr size_t kSSmallElems = 2200000;   // 256 blocks of one 32 x 256 item
+
+inline bool stream_without_token(int d_ff, int d_model, int count, int chunk, bool nt) {
+  const int parts = stream_parts(d_ff, d_model);
+  if (parts * kSTM >= d_ff && size_t(d_ff) * d_model * count <= kSSmallElems) return true;
+  const int blocks = (d_model + kSTN - 1) / kSTN * parts * count;
+  return blocks > kSSlots * 15 / 16 && blocks <= kSSlots && ((nt && chunk <= 16) || d_model % 64 != 0);
+}
+
 constexpr int kRTM = 64;                 // register-operand kernels: rows per wave
 constexpr int kRMaxC = 384;              // largest chunk without a fused token on this path
 
@@ -175,6 +196,8 @@ inline WriteRoute write_route(bool io_bf16, bool state_bf16, int d_ff, int d_mod
   }
   r.read_first = token;
   if (!state_bf16 && chunk <= kRMaxC) r.kernel = WriteKernel::rows;
+  if (state_bf16 && chunk <= kSMaxC && stream_without_token(d_ff, d_model, count, chunk, r.nt))
+    r.kernel = WriteKernel::stream;
   return r;
 }
 

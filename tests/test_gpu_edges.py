@@ -172,11 +172,14 @@ def test_read_routes_agree_bit_for_bit(d_ff, d_model, io, state, n):
 # matrix, a tile of 64 x 64 and its remainders (8 rows in a lane's second run,
 # one column group past the tile), a count of tiles no block of four divides;
 # chunk: one, a group of 16 and past it, the last of this path and the first of
-# the GEMM.  bf16 state, GEMM: chunks of one and two stages of 32 ranks
+# the GEMM.  bf16 state: streaming and GEMM on both sides of the small-state line
+# (2.2 M elements of a group, one item a block), chunks of one and two GEMM stages
+# of 32 ranks; a row of GEMM tiles and a column of them, fewer than the XCDs
 ROWS_WRITES = [
     (8, 8, "f32", 1), (64, 64, "f32", 16), (72, 72, "f32", 17), (136, 328, "f32", 33), (248, 1032, "f32", 64),
     (520, 264, "f32", 384), (520, 264, "f32", 385), (8, 8, "bf16", 1), (264, 136, "bf16", 31), (520, 136, "bf16", 33),
-    (264, 264, "bf16", 64),
+    (264, 264, "bf16", 64), (2048, 512, "bf16", 17), (2056, 512, "bf16", 64), (1544, 1032, "bf16", 33),
+    (72, 16392, "bf16", 64), (8200, 72, "bf16", 20), (264, 4104, "bf16", 70),
 ]
 
 

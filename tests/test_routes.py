@@ -70,3 +70,19 @@ def test_few_gemm_tiles_reach_every_xcd(ask, count, d_ff, d_model):
     (once, *xcds), = ask(f"gemm {count} {mt} {nt}")
     assert once == "1"
     assert max(map(int, xcds)) - min(map(int, xcds)) <= 1
+
+
+def test_small_bf16_states_without_a_token_stream(ask):
+    """bf16 state, C <= 64: the streaming kernel up to one item a CU (both sides
+    of the line), and one owner whose blocks fill its slots."""
+    def kernel(d_ff, d_model, count, chunk):
+        (k, *_), = ask(f"write bf16 bf16 {d_ff} {d_model} {count} {chunk} 0")
+        return k
+    for small in ((8, 8, 1), (264, 136, 8), (1000, 264, 8), (1024, 1024, 2), (2048, 512, 2), (256, 4096, 2)):
+        assert kernel(*small, 1) == kernel(*small, 64) == "stream", small
+        assert kernel(*small, 65) == "gemm", small
+    for large in ((512, 2048, 4), (1024, 1024, 4), (2048, 512, 4), (5000, 128, 1), (8192, 64, 1), (9728, 2560, 2)):
+        assert kernel(*large, 1) == kernel(*large, 64) == "gemm", large
+    assert kernel(9728, 2560, 1, 16) == kernel(14336, 4096, 1, 16) == "stream"
+    assert kernel(9728, 2560, 1, 48) == kernel(14336, 4096, 1, 48) == "gemm"
+    assert kernel(10000, 2000, 1, 64) == "stream"
