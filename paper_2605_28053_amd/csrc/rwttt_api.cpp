@@ -286,6 +286,12 @@ rwttt_status rwttt_plan(const rwttt_ctx* ctx, const rwttt_event* ev, uint32_t n_
 
 namespace {
 
+// Live states and W0s of all owners and layers.
+size_t context_bytes_of(const rwttt_ctx* ctx) {
+  const rwttt_config& c = ctx->cfg;
+  return size_t(c.n_layers) * (c.n_owners * slot_bytes_of(&c) + size_t(c.d_ff) * c.d_model * ctx->io_bytes());
+}
+
 // Defence in depth beside the planner (Section 3, eq. compatibility): every
 // member must still be at the version the caller planned it at.
 bool versions_match(const rwttt_ctx* ctx, const uint32_t* owners, const uint64_t* expected, uint32_t n) {
@@ -343,6 +349,7 @@ rwttt_status read_impl(rwttt_ctx* ctx, const rwttt_group* group, const uint32_t*
   }
 
   rwttt::ReadLaunch L;
+  L.context_bytes = context_bytes_of(ctx);
   L.io_bf16 = ctx->cfg.io_dtype == RWTTT_BF16;
   L.state_bf16 = ctx->cfg.state_dtype == RWTTT_BF16;
   L.d_ff = int(ctx->cfg.d_ff);
@@ -400,6 +407,7 @@ rwttt_status rwttt_read_noalloc(rwttt_ctx* ctx, const rwttt_group* group, const 
     return RWTTT_E_CAPACITY;
 
   rwttt::ReadLaunch L;
+  L.context_bytes = context_bytes_of(ctx);
   L.io_bf16 = ctx->cfg.io_dtype == RWTTT_BF16;
   L.state_bf16 = state_bf16;
   L.d_ff = int(ctx->cfg.d_ff);
@@ -481,6 +489,7 @@ rwttt_status rwttt_write(rwttt_ctx* ctx, const rwttt_group* group, const uint32_
   }
 
   rwttt::WriteLaunch L;
+  L.context_bytes = context_bytes_of(ctx);
   L.io_bf16 = ctx->cfg.io_dtype == RWTTT_BF16;
   L.state_bf16 = ctx->cfg.state_dtype == RWTTT_BF16;
   L.d_ff = int(ctx->cfg.d_ff);

@@ -28,6 +28,7 @@ ReadGeometry read_geometry(int d_ff, int d_model, int state_bf16, int n_owners);
 struct ReadLaunch {
   int io_bf16, state_bf16;
   int d_ff, d_model, count, n_owners;
+  size_t context_bytes;      // live states and W0s of all owners and layers
   const void* x;             // [n_owners, d_ff], owner-indexed
   void* y;                   // [n_owners, d_model], owner-indexed
   const void* w0;            // [d_ff, d_model]
@@ -48,6 +49,7 @@ struct TailLaunch {
 struct WriteLaunch {
   int io_bf16, state_bf16;
   int d_ff, d_model, count, chunk, n_owners;
+  size_t context_bytes;      // live states and W0s of all owners and layers
   float eta;
   const void* x;             // token inputs [n_owners, d_ff], or null for no token
   void* y;                   // token outputs [n_owners, d_model]

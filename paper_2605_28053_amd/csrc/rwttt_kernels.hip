@@ -1312,7 +1312,7 @@ hipError_t launch_read_t(const ReadLaunch& L, hipStream_t stream, float* slot_pa
     p.row[b] = b < L.count ? L.row[b] : 0u;
     p.tail[b] = b < L.count ? L.tail[b] : nullptr;
   }
-  const ReadRoute route = read_route(sizeof(IO) == 2, sizeof(ST) == 2, L.d_ff, L.d_model, L.count);
+  const ReadRoute route = read_route(sizeof(IO) == 2, sizeof(ST) == 2, L.d_ff, L.d_model, L.count, L.context_bytes);
   if (route.direct) {
     constexpr int tile = kDirectLanes * read_cols_per_lane(sizeof(ST) == 2);
     p.nt = (L.d_model + tile - 1) / tile;
@@ -1362,7 +1362,8 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
     p.row[b] = in ? L.row[b] : 0u;
   }
   const bool token = L.x != nullptr;
-  const WriteRoute route = write_route(L.io_bf16, sizeof(ST) == 2, L.d_ff, L.d_model, L.count, L.chunk, token);
+  const WriteRoute route = write_route(L.io_bf16, sizeof(ST) == 2, L.d_ff, L.d_model, L.count, L.chunk, token,
+                                       L.context_bytes);
   const ReadGeometry geo = read_geometry(L.d_ff, L.d_model, L.state_bf16, L.n_owners);
   // the fused token's partials, p.parts rows of p.npadw per owner
   auto reduce_token = [&] {
@@ -1439,7 +1440,7 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
         p.tpart = reinterpret_cast<float*>(static_cast<char*>(L.workspace) + geo.token_offset);
         hipLaunchKernelGGL((write_stream_kernel<ST, true, NT>), grid, dim3(256), 0, stream, p);
         reduce_token();
-      } else if constexpr (sizeof(ST) == 2) {
+      } else if constexpr (sizeof(ST) == 2 && NT) {
         hipLaunchKernelGGL((write_stream_kernel<ST, false, NT>), grid, dim3(256), 0, stream, p);
       }
     };
@@ -1451,6 +1452,7 @@ hipError_t launch_write_t(const WriteLaunch& L, hipStream_t stream) {
     // no fused kernel on this path: the token is an ordinary READ of the group at version v
     ReadLaunch R;
     R.io_bf16 = L.io_bf16;
+    R.context_bytes = L.context_bytes;
     R.state_bf16 = L.state_bf16;
     R.d_ff = L.d_ff;
     R.d_model = L.d_model;

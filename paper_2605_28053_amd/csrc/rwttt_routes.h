@@ -18,20 +18,23 @@ constexpr int kReadChunk = 256;       // K rows per work item
 constexpr int read_cols_per_lane(int state_bf16) { return state_bf16 ? 8 : 4; }   // 16 B per lane
 constexpr int read_tile_n(int state_bf16) { return 64 * read_cols_per_lane(state_bf16); }
 
-// Whether the live state that a call reads is little enough to leave in the 256
-// MB last-level cache for the calls after it: loaded without the non-temporal
-// hint it stays there, several such states beside each other, and a later call
-// finds it.  In us without / with the hint, calls on three states in turn, then
-// on six (so that the last-level cache is too small): READ of four owners of 2048
-// x 2048 bf16 (42 MB) 11.8 / 16.4, 15.4 / 16.5; WRITE of two of 3072 x 1024
-// (25 MB) 9.0 / 10.3, 9.0 / 10.6, of eight of 600 x 2000 (38 MB) 14.8 / 19.7,
-// 18.6 / 20.0.  Above, the states push each other out and the hint is better:
-// READ of one owner of 9728 x 2560 (149 MB) 31.8 / 27.4 us, and a large READ
-// would push W0 out of L2 (eight owners 147 / 128 us).  Stores always have the
-// hint: a candidate kept in the cache takes the place of a live state (one WRITE
-// of 9728 x 2560, C = 64, 54.6 against 48.1 us).  The GEMM keeps it for its live tiles too: its evidence lives
-// in L2 (62.2 against 59.6 us for 11 owners of 5448 x 288 bf16, C = 650).
-inline bool stays_cached(size_t live_bytes) { return live_bytes <= 48000000; }
+// Whether a context's live states and W0s stay in the 256 MB last-level cache
+// from one pass over them to the next: a serving step visits every owner and
+// layer before it comes back to a state, so what counts is the context, not the
+// call.  Loaded without the non-temporal hint they stay there and the next pass
+// finds them; in a larger context the next pass finds nothing, and the hint is
+// better because such loads leave no lines to be pushed out.  In us with / without
+// it, passes over 209 to 251 MB, then over 400 to 750 MB: READ of two owners of
+// 2048 x 2048 13.6 / 11.1, 13.7 / 14.6; of four with bf16 state 15.9 / 12.0, 16.0 /
+// 16.7; of one of 4864 x 2560 19.0 / 15.9, 19.1 / 20.6; WRITE of one owner of 1024 x
+// 1024, C = 64, 5.5 / 5.4, 5.5 / 6.2; of four of 2048 x 2048 with a token 32.6 / 29.3,
+// 32.6 / 33.4; fp32 evidence, three of 3600 x 1512, C = 4, 30.5 / 23.6 (195 MB),
+// 30.9 / 30.3.  At 300 MB the two sides meet for calls of any size (4 to 150 MB).
+// Stores always have the hint: a candidate kept in the cache takes the place of
+// a live state (one WRITE of 9728 x 2560, C = 64, 54.6 against 48.1 us).  The GEMM
+// keeps it for its live tiles too: its evidence lives in L2 (62.2 against 59.6 us
+// for 11 owners of 5448 x 288 bf16, C = 650).
+inline bool stays_cached(size_t context_bytes) { return context_bytes <= 256000000; }
 
 // ---------------------------------------------------------------------------
 // READ
@@ -51,12 +54,14 @@ struct ReadRoute {
   bool nt;                   // live state loaded with the non-temporal hint
 };
 
-inline ReadRoute read_route(bool io_bf16, bool state_bf16, int d_ff, int d_model, int count) {
+// context_bytes: live states and W0s of all owners and layers
+inline ReadRoute read_route(bool io_bf16, bool state_bf16, int d_ff, int d_model, int count,
+                            size_t context_bytes) {
   const size_t io = io_bf16 ? 2 : 4, state = state_bf16 ? 2 : 4;
   const size_t bytes = size_t(d_ff) * d_model * (count * state + io);
   ReadRoute r;
   r.direct = d_ff <= kDirectRows && bytes <= kDirectBytes;
-  r.nt = !stays_cached(bytes);
+  r.nt = !stays_cached(context_bytes);
   // leaves of eight rows where the one launch above must match, and for fp32 io
   // with bf16 state, where they are faster (20.0 against 23.4 us for two owners
   // of 3600 x 1512)
@@ -95,7 +100,7 @@ inline int stream_parts(int d_ff, int d_model) {
 //   sooner: 4.5 / 5.6 at 264 x 136, 4.8 / 5.7 at 1000 x 264 x 2, 5.0 / 5.6 at 1024
 //   x 1024 x 2, all C = 1; 5.4 / 5.9 at 2048 x 512, C = 64.  Past it 7.5 / 6.4 at
 //   512 x 2048 x 4, C = 64, and 7.7 / 5.4 at 5000 x 128 (three items a block);
-// * one round of blocks that fills the slots, state from HBM and one stage of
+// * one owner whose blocks fill the slots once, state from HBM and one stage of
 //   evidence: 21.2 / 22.2 at 9728 x 2560, 43.4 / 45.1 at 14336 x 4096, C = 16 (the
 //   latter 46.4 / 46.0 at C = 48); rows that are no whole 128-byte lines cost the
 //   GEMM's narrower tiles more, at every C: 21.0 / 23.8 at 10000 x 2000.
@@ -104,8 +109,8 @@ constexpr size_t kSSmallElems = 2200000;   // 256 blocks of one 32 x 256 item
 inline bool stream_without_token(int d_ff, int d_model, int count, int chunk, bool nt) {
   const int parts = stream_parts(d_ff, d_model);
   if (parts * kSTM >= d_ff && size_t(d_ff) * d_model * count <= kSSmallElems) return true;
-  const int blocks = (d_model + kSTN - 1) / kSTN * parts * count;
-  return blocks > kSSlots * 15 / 16 && blocks <= kSSlots && ((nt && chunk <= 16) || d_model % 64 != 0);
+  const int blocks = (d_model + kSTN - 1) / kSTN * parts;
+  return count == 1 && blocks > kSSlots * 15 / 16 && blocks <= kSSlots && ((nt && chunk <= 16) || d_model % 64 != 0);
 }
 
 constexpr int kRTM = 64;                 // register-operand kernels: rows per wave
@@ -181,9 +186,9 @@ struct WriteRoute {
 };
 
 inline WriteRoute write_route(bool io_bf16, bool state_bf16, int d_ff, int d_model, int count, int chunk,
-                              bool token) {
+                              bool token, size_t context_bytes) {
   WriteRoute r = {WriteKernel::gemm, false, 0, true};
-  r.nt = !stays_cached(size_t(d_ff) * d_model * count * (state_bf16 ? 2 : 4));
+  r.nt = !stays_cached(context_bytes);
   if (!io_bf16) {
     r.kernel = WriteKernel::f32;
     // without a token nothing limits the rows of a block
@@ -196,8 +201,10 @@ inline WriteRoute write_route(bool io_bf16, bool state_bf16, int d_ff, int d_mod
   }
   r.read_first = token;
   if (!state_bf16 && chunk <= kRMaxC) r.kernel = WriteKernel::rows;
-  if (state_bf16 && chunk <= kSMaxC && stream_without_token(d_ff, d_model, count, chunk, r.nt))
+  if (state_bf16 && chunk <= kSMaxC && stream_without_token(d_ff, d_model, count, chunk, r.nt)) {
     r.kernel = WriteKernel::stream;
+    r.nt = true;             // also in a small context: 4.8 / 5.1 us with / without at 512 x 2048, C = 1
+  }
   return r;
 }
 

@@ -1,7 +1,7 @@
 // Prints the dispatch rules' answers, one line for each query line of stdin:
-//   read io state d_ff d_model count                -> direct waves leaf nt
-//   write io state d_ff d_model count chunk token   -> kernel read_first wn nt
-//   gemm count mt ntl                               -> 1 if every tile is dealt once, then tiles of each XCD
+//   read io state d_ff d_model count context_bytes                -> direct waves leaf nt
+//   write io state d_ff d_model count chunk token context_bytes   -> kernel read_first wn nt
+//   gemm count mt ntl                                             -> 1 if every tile is dealt once, then tiles of each XCD
 #include <cstdio>
 #include <iostream>
 #include <string>
@@ -27,13 +27,16 @@ int main() {
   while (std::cin >> what) {
     if (what == "read") {
       int d_ff, d_model, count;
-      std::cin >> io >> state >> d_ff >> d_model >> count;
-      const ReadRoute r = read_route(io == "bf16", state == "bf16", d_ff, d_model, count);
+      size_t context;
+      std::cin >> io >> state >> d_ff >> d_model >> count >> context;
+      const ReadRoute r = read_route(io == "bf16", state == "bf16", d_ff, d_model, count, context);
       std::printf("%d %d %d %d\n", r.direct, r.waves, r.leaf, r.nt);
     } else if (what == "write") {
       int d_ff, d_model, count, chunk, token;
-      std::cin >> io >> state >> d_ff >> d_model >> count >> chunk >> token;
-      const WriteRoute r = write_route(io == "bf16", state == "bf16", d_ff, d_model, count, chunk, token != 0);
+      size_t context;
+      std::cin >> io >> state >> d_ff >> d_model >> count >> chunk >> token >> context;
+      const WriteRoute r =
+          write_route(io == "bf16", state == "bf16", d_ff, d_model, count, chunk, token != 0, context);
       std::printf("%s %d %d %d\n", name(r.kernel), r.read_first, r.wn, r.nt);
     } else if (what == "gemm") {
       int count, mt, ntl;

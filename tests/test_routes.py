@@ -9,6 +9,7 @@ import subprocess
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+BIG = 10 ** 9                          # a context that no cache holds
 READ_CHUNK, TOKEN_ROWS = 256, 64       # K rows of a READ partial; an owner's token partials at most
 DTYPES = [("bf16", "f32"), ("bf16", "bf16"), ("f32", "f32"), ("f32", "bf16")]
 # the smallest matrix, ragged and power-of-two ones, the full shapes
@@ -35,10 +36,10 @@ def test_an_owners_order_of_addition_does_not_depend_on_the_group(ask):
     for io, state in DTYPES:
         for d_ff, d_model in SHAPES:
             counts = (1, 2, 3, 8, 64)
-            reads = ask(*(f"read {io} {state} {d_ff} {d_model} {n}" for n in counts))
+            reads = ask(*(f"read {io} {state} {d_ff} {d_model} {n} {BIG}" for n in counts))
             assert len({leaf for _, _, leaf, _ in reads}) == 1
             assert all(d_ff <= 1536 and leaf == "8" for direct, _, leaf, _ in reads if direct == "1")
-            tokens = ask(*(f"write {io} {state} {d_ff} {d_model} {n} 40 1" for n in counts))
+            tokens = ask(*(f"write {io} {state} {d_ff} {d_model} {n} 40 1 {BIG}" for n in counts))
             assert len({(kernel, first, wn) for kernel, first, wn, _ in tokens}) == 1
 
 
@@ -46,7 +47,7 @@ def test_token_partials_fit_an_owners_workspace(ask):
     """Rows of partial sums per owner: 64 of them, or one per READ chunk."""
     for io, state in DTYPES:
         for d_ff, d_model in SHAPES:
-            (kernel, _, wn, _), = ask(f"write {io} {state} {d_ff} {d_model} 3 33 1")
+            (kernel, _, wn, _), = ask(f"write {io} {state} {d_ff} {d_model} 3 33 1 {BIG}")
             if kernel == "rows_token":
                 assert -(-d_ff // 64) <= TOKEN_ROWS
             elif kernel == "f32" and wn != "1":
@@ -76,7 +77,7 @@ def test_small_bf16_states_without_a_token_stream(ask):
     """bf16 state, C <= 64: the streaming kernel up to one item a CU (both sides
     of the line), and one owner whose blocks fill its slots."""
     def kernel(d_ff, d_model, count, chunk):
-        (k, *_), = ask(f"write bf16 bf16 {d_ff} {d_model} {count} {chunk} 0")
+        (k, *_), = ask(f"write bf16 bf16 {d_ff} {d_model} {count} {chunk} 0 {BIG}")
         return k
     for small in ((8, 8, 1), (264, 136, 8), (1000, 264, 8), (1024, 1024, 2), (2048, 512, 2), (256, 4096, 2)):
         assert kernel(*small, 1) == kernel(*small, 64) == "stream", small
@@ -86,3 +87,15 @@ def test_small_bf16_states_without_a_token_stream(ask):
     assert kernel(9728, 2560, 1, 16) == kernel(14336, 4096, 1, 16) == "stream"
     assert kernel(9728, 2560, 1, 48) == kernel(14336, 4096, 1, 48) == "gemm"
     assert kernel(10000, 2000, 1, 64) == "stream"
+
+
+def test_the_cache_hint_follows_the_context_not_the_call(ask):
+    """Calls of any size keep the non-temporal hint where the context's live
+    states and W0s do not fit the last-level cache, and drop it where they do."""
+    for io, state in DTYPES:
+        for d_ff, d_model, count in ((1024, 1024, 1), (2048, 2048, 2), (3600, 1512, 3), (9728, 2560, 1)):
+            for context, nt in ((256000000, "0"), (256000001, "1"), (2 * BIG, "1")):
+                call = f"{io} {state} {d_ff} {d_model} {count}"
+                queries = [f"read {call} {context}", f"write {call} 100 0 {context}", f"write {call} 16 1 {context}"]
+                for answer in ask(*queries):
+                    assert answer[-1] == nt or answer[0] == "gemm", (call, context)
