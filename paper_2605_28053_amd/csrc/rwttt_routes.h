@@ -18,23 +18,31 @@ constexpr int kReadChunk = 256;       // K rows per work item
 constexpr int read_cols_per_lane(int state_bf16) { return state_bf16 ? 8 : 4; }   // 16 B per lane
 constexpr int read_tile_n(int state_bf16) { return 64 * read_cols_per_lane(state_bf16); }
 
-// Whether a context's live states and W0s stay in the 256 MB last-level cache
-// from one pass over them to the next: a serving step visits every owner and
-// layer before it comes back to a state, so what counts is the context, not the
-// call.  Loaded without the non-temporal hint they stay there and the next pass
-// finds them; in a larger context the next pass finds nothing, and the hint is
-// better because such loads leave no lines to be pushed out.  In us with / without
-// it, passes over 209 to 251 MB, then over 400 to 750 MB: READ of two owners of
-// 2048 x 2048 13.6 / 11.1, 13.7 / 14.6; of four with bf16 state 15.9 / 12.0, 16.0 /
-// 16.7; of one of 4864 x 2560 19.0 / 15.9, 19.1 / 20.6; WRITE of one owner of 1024 x
-// 1024, C = 64, 5.5 / 5.4, 5.5 / 6.2; of four of 2048 x 2048 with a token 32.6 / 29.3,
-// 32.6 / 33.4; fp32 evidence, three of 3600 x 1512, C = 4, 30.5 / 23.6 (195 MB),
-// 30.9 / 30.3.  At 300 MB the two sides meet for calls of any size (4 to 150 MB).
+// Whether the live state that a call reads (call_bytes) is loaded without the
+// non-temporal hint, to stay in the 256 MB last-level cache until the next call
+// that reads it.  A serving step visits every owner and layer before it comes back
+// to a state, so a context whose live states and W0s (context_bytes) do not fit the
+// cache keeps the hint: such loads leave no lines to be pushed out.  A context
+// that fits may still share the cache, with other contexts or the rest of a model;
+// a large call then loses more than it could win.  In us with / without the hint,
+// by the bytes of the states visited in turn:
+// * READ of two owners of 2048 x 2048 (42 MB) 13.3 / 10.9 up to 209 MB, 13.4 / 14.6 at
+//   330 MB; WRITE of four of 2048 x 2048 with token (67 MB) 30.9 / 27.0 at 225 MB, 31.2 /
+//   32.7 at 600 MB;
+// * READ of one owner of 9728 x 2560 (149 MB) 27.4 / 25.2 when it is alone, 27.3 /
+//   28.8 when two such contexts take turns, 27.4 / 31.6 with four; five of 5000 x
+//   1528 (168 MB) 35.1 / 31.1, 36.0 / 36.7, 36.1 / 38.6; WRITE of one of 9728 x 2560
+//   with token 47.8 / 44.0, 47.8 / 49.0, 47.8 / 51.3.
 // Stores always have the hint: a candidate kept in the cache takes the place of
 // a live state (one WRITE of 9728 x 2560, C = 64, 54.6 against 48.1 us).  The GEMM
 // keeps it for its live tiles too: its evidence lives in L2 (62.2 against 59.6 us
 // for 11 owners of 5448 x 288 bf16, C = 650).
-inline bool stays_cached(size_t context_bytes) { return context_bytes <= 256000000; }
+constexpr size_t kCacheContext = 256000000;
+constexpr size_t kCacheCall = 48000000;
+
+inline bool stays_cached(size_t call_bytes, size_t context_bytes) {
+  return call_bytes <= kCacheCall && context_bytes <= kCacheContext;
+}
 
 // ---------------------------------------------------------------------------
 // READ
@@ -61,7 +69,7 @@ inline ReadRoute read_route(bool io_bf16, bool state_bf16, int d_ff, int d_model
   const size_t bytes = size_t(d_ff) * d_model * (count * state + io);
   ReadRoute r;
   r.direct = d_ff <= kDirectRows && bytes <= kDirectBytes;
-  r.nt = !stays_cached(context_bytes);
+  r.nt = !stays_cached(bytes, context_bytes);
   // leaves of eight rows where the one launch above must match, and for fp32 io
   // with bf16 state, where they are faster (20.0 against 23.4 us for two owners
   // of 3600 x 1512)
@@ -106,11 +114,12 @@ inline int stream_parts(int d_ff, int d_model) {
 //   GEMM's narrower tiles more, at every C: 21.0 / 23.8 at 10000 x 2000.
 constexpr size_t kSSmallElems = 2200000;   // 256 blocks of one 32 x 256 item
 
-inline bool stream_without_token(int d_ff, int d_model, int count, int chunk, bool nt) {
+inline bool stream_without_token(int d_ff, int d_model, int count, int chunk, size_t context_bytes) {
   const int parts = stream_parts(d_ff, d_model);
   if (parts * kSTM >= d_ff && size_t(d_ff) * d_model * count <= kSSmallElems) return true;
   const int blocks = (d_model + kSTN - 1) / kSTN * parts;
-  return count == 1 && blocks > kSSlots * 15 / 16 && blocks <= kSSlots && ((nt && chunk <= 16) || d_model % 64 != 0);
+  return count == 1 && blocks > kSSlots * 15 / 16 && blocks <= kSSlots && 
+         ((context_bytes > kCacheContext && chunk <= 16) || d_model % 64 != 0);
 }
 
 constexpr int kRTM = 64;                 // register-operand kernels: rows per wave
@@ -188,7 +197,7 @@ struct WriteRoute {
 inline WriteRoute write_route(bool io_bf16, bool state_bf16, int d_ff, int d_model, int count, int chunk,
                               bool token, size_t context_bytes) {
   WriteRoute r = {WriteKernel::gemm, false, 0, true};
-  r.nt = !stays_cached(context_bytes);
+  r.nt = !stays_cached(size_t(d_ff) * d_model * count * (state_bf16 ? 2 : 4), context_bytes);
   if (!io_bf16) {
     r.kernel = WriteKernel::f32;
     // without a token nothing limits the rows of a block
@@ -201,7 +210,7 @@ inline WriteRoute write_route(bool io_bf16, bool state_bf16, int d_ff, int d_mod
   }
   r.read_first = token;
   if (!state_bf16 && chunk <= kRMaxC) r.kernel = WriteKernel::rows;
-  if (state_bf16 && chunk <= kSMaxC && stream_without_token(d_ff, d_model, count, chunk, r.nt)) {
+  if (state_bf16 && chunk <= kSMaxC && stream_without_token(d_ff, d_model, count, chunk, context_bytes)) {
     r.kernel = WriteKernel::stream;
     r.nt = true;             // also in a small context: 4.8 / 5.1 us with / without at 512 x 2048, C = 1
   }

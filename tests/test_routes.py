@@ -89,13 +89,15 @@ def test_small_bf16_states_without_a_token_stream(ask):
     assert kernel(10000, 2000, 1, 64) == "stream"
 
 
-def test_the_cache_hint_follows_the_context_not_the_call(ask):
-    """Calls of any size keep the non-temporal hint where the context's live
-    states and W0s do not fit the last-level cache, and drop it where they do."""
+def test_the_cache_hint_follows_the_call_and_its_context(ask):
+    """The hint is dropped where the context's live states and W0s fit the
+    last-level cache and the call is small beside it; never where only one of the
+    two holds.  Both sides of both lines."""
+    sizes = ((1024, 1024, 1, True), (2000, 2000, 2, True), (3600, 1512, 5, False), (9728, 2560, 2, False))
     for io, state in DTYPES:
-        for d_ff, d_model, count in ((1024, 1024, 1), (2048, 2048, 2), (3600, 1512, 3), (9728, 2560, 1)):
-            for context, nt in ((256000000, "0"), (256000001, "1"), (2 * BIG, "1")):
+        for d_ff, d_model, count, small in sizes:
+            for context, fits in ((256000000, True), (256000001, False), (2 * BIG, False)):
                 call = f"{io} {state} {d_ff} {d_model} {count}"
                 queries = [f"read {call} {context}", f"write {call} 100 0 {context}", f"write {call} 16 1 {context}"]
                 for answer in ask(*queries):
-                    assert answer[-1] == nt or answer[0] == "gemm", (call, context)
+                    assert answer[0] == "gemm" or answer[-1] == ("0" if fits and small else "1"), (call, context)
