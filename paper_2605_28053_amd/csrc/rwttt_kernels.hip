@@ -237,7 +237,6 @@ __global__ void __launch_bounds__(256) read_reduce_kernel(const ReadParams p) {
 // the call) against 11.2 before, four of 976 x 1920 8.1 against 16.8.  The same
 // tree over the same leaves of eight rows as the two launches.
 constexpr int kDirectThreads = 1024;
-constexpr int kDirectLanes = 8;
 constexpr int kDirectGroups = kDirectThreads / kDirectLanes;
 constexpr int kDirectLeaf = kUnroll;
 static_assert(kDirectRows <= 2 * kDirectGroups * kDirectLeaf && kDirectRows <= kTreeChunks * kReadChunk, "");

@@ -5,6 +5,7 @@
 #pragma once
 
 #include <stddef.h>
+#include <stdint.h>
 
 #include <algorithm>
 
@@ -48,13 +49,23 @@ inline bool stays_cached(size_t call_bytes, size_t context_bytes) {
 // READ
 // ---------------------------------------------------------------------------
 
-// Where the two launches are better than one (read_direct_kernel): a block's column of LEAVES leaves reaches
-// only about 70 GB/s, and 128-byte runs 4 TB/s over the chip.  One launch
-// against two, in us: 8.0/11.8 at 1024 x 512 x 4 owners, 8.5/12.2 at 512 x
-// 4096 x 4 (38 MB), 15.9/14.0 at 512 x 4096 x 8 (71 MB), 10.6/12.9 at 1056 x
-// 1008 x 6, 12.5/11.6 at 2048 x 512 x 4.
-constexpr size_t kDirectBytes = 36000000;
+// Where the two launches are better than one (read_direct_kernel), all with the
+// state from HBM, one launch / two in us:
+// * a block's column of leaves reaches only about 70 GB/s, so one launch needs few
+//   bytes: 11.2 / 14.3 at 512 x 4096 x 4 and 10.6 / 14.4 at 1024 x 2048 x 4 (38 MB),
+//   but 16.3 / 14.9 at 1024 x 2048 x 5 (46 MB), 19.0 / 15.6 at 1000 x 3000 x 3 (42 MB);
+// * a block of 16 waves takes 1.5 to 2 us of its CU however few rows it has, and
+//   one fits a CU (two of bf16 io with fp32 state, the form with the fewest
+//   registers), so one launch needs few blocks: bf16 io and state 8.5 / 15.2 at 256 x
+//   4096 x 8 (512 blocks), 11.6 / 12.0 at 128 x 14336 x 4 (896), 16.1 / 12.5 at 128 x
+//   14336 x 6 (1344), 25.0 / 8.7 at 8 x 14336 x 16 (3584); fp32 14.5 / 10.1 at 64 x
+//   14336 x 4 (1792); bf16 io, fp32 state 12.3 / 14.6 at 256 x 2048 x 18 (1152), 12.4 /
+//   12.2 at 128 x 14336 x 4 (1792).
+constexpr size_t kDirectBytes = 38000000;
 constexpr int kDirectRows = 1536;          // at most two leaves per row group
+constexpr int kDirectLanes = 8;            // lanes of 16 bytes side by side: a block's columns
+constexpr int kDirectBlocks = 1024;
+constexpr int kDirectBlocksTwo = 1536;     // where two blocks fit a CU
 
 struct ReadRoute {
   bool direct;               // one launch
@@ -68,7 +79,10 @@ inline ReadRoute read_route(bool io_bf16, bool state_bf16, int d_ff, int d_model
   const size_t io = io_bf16 ? 2 : 4, state = state_bf16 ? 2 : 4;
   const size_t bytes = size_t(d_ff) * d_model * (count * state + io);
   ReadRoute r;
-  r.direct = d_ff <= kDirectRows && bytes <= kDirectBytes;
+  const int tile = kDirectLanes * read_cols_per_lane(state_bf16);
+  const int64_t blocks = int64_t((d_model + tile - 1) / tile) * count;
+  r.direct = d_ff <= kDirectRows && bytes <= kDirectBytes &&
+             blocks <= (io_bf16 && !state_bf16 ? kDirectBlocksTwo : kDirectBlocks);
   r.nt = !stays_cached(bytes, context_bytes);
   // leaves of eight rows where the one launch above must match, and for fp32 io
   // with bf16 state, where they are faster (20.0 against 23.4 us for two owners

@@ -132,14 +132,14 @@ def test_f32_write_keeps_non_finite_evidence_in_its_place():
     assert torch.equal(bad, want)
 
 
-# READs of up to 1536 rows run as one launch for 36 MB of state and W0, as two
-# above: a group on each side must give an owner the same bits.  Rows: one leaf
-# of 8, one leaf per row group (1024) and past it, the limit and past it (always
-# two launches); the last column tile is ragged
+# READs of up to 1536 rows run as one launch for 38 MB of state and W0 and 1024
+# blocks, as two above: a group on each side must give an owner the same bits.
+# Rows: one leaf of 8, one leaf per row group (1024) and past it, the limit and past
+# it (always two launches); the last column tile is ragged
 READ_ROUTES = [
     (264, 4104, "bf16", "f32", 12), (1024, 2056, "bf16", "bf16", 9), (1032, 2056, "bf16", "f32", 5),
     (1536, 1032, "f32", "f32", 8), (1544, 1032, "bf16", "f32", 8), (3600, 520, "f32", "bf16", 3),
-    (8, 8, "f32", "f32", 2), (16, 72, "bf16", "f32", 3),
+    (8, 8, "f32", "f32", 2), (16, 72, "bf16", "f32", 3), (8, 8200, "bf16", "bf16", 8), (16, 8200, "bf16", "f32", 6),
 ]
 
 

@@ -73,6 +73,21 @@ def test_few_gemm_tiles_reach_every_xcd(ask, count, d_ff, d_model):
     assert max(map(int, xcds)) - min(map(int, xcds)) <= 1
 
 
+def test_one_launch_read_needs_few_rows_bytes_and_blocks(ask):
+    """Both sides of each limit: 1536 rows; 38 MB of state and W0; 1024 blocks of
+    32 (bf16 state: 64) columns of one owner, 1536 for bf16 io with fp32 state."""
+    one = [("bf16", "f32", 1536, 1032, 4), ("bf16", "f32", 512, 4096, 4), ("bf16", "bf16", 512, 4096, 8),
+           ("bf16", "bf16", 128, 14336, 4), ("bf16", "bf16", 8, 4096, 16), ("f32", "f32", 64, 14336, 2),
+           ("f32", "bf16", 32, 8192, 8), ("bf16", "f32", 256, 2048, 16), ("bf16", "f32", 8, 8192, 6)]
+    two = [("bf16", "f32", 1544, 1032, 4), ("bf16", "f32", 512, 4096, 5), ("f32", "f32", 512, 4096, 4),
+           ("bf16", "bf16", 128, 14336, 6), ("bf16", "bf16", 8, 4104, 16), ("bf16", "bf16", 8, 14336, 16),
+           ("f32", "f32", 64, 14336, 4), ("f32", "bf16", 8, 14336, 8), ("bf16", "f32", 8, 8200, 6),
+           ("bf16", "f32", 8, 1 << 20, 16)]
+    for call, direct in [(c, "1") for c in one] + [(c, "0") for c in two]:
+        (d, *_), = ask("read " + " ".join(map(str, call)) + f" {BIG}")
+        assert d == direct, call
+
+
 def test_small_bf16_states_without_a_token_stream(ask):
     """bf16 state, C <= 64: the streaming kernel up to one item a CU (both sides
     of the line), and one owner whose blocks fill its slots."""
