@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(64 * NW) read_partial_kernel(const ReadParams 
   // leaves of LEAF rows, each a chain from zero, eight rows' loads in flight at
   // once (eight rows are inside or outside the matrix together)
   constexpr int NL = RW / LEAF;
-  constexpr int LV = NL == 4 ? 3 : NL;                   // log2(NL) + 1
+  constexpr int LV = NL == 8 ? 4 : NL == 4 ? 3 : NL;     // log2(NL) + 1
   float stack[LV][COLS];
   const ST* dbase = static_cast<const ST*>(p.dw[b]) + size_t(k0) * p.d_model + col;
   const IO* wbase = static_cast<const IO*>(p.w0) + size_t(k0) * p.d_model + col;
@@ -1326,12 +1326,20 @@ hipError_t launch_read_t(const ReadLaunch& L, hipStream_t stream, float* slot_pa
   const dim3 grid(unsigned((g.ks * g.nt + 7) / 8 * 8) * unsigned(L.count));
   auto run = [&](auto nt) {
     constexpr bool NT = decltype(nt)::value;
-    if (route.leaf == kDirectLeaf)
+    if (route.leaf == kDirectLeaf) {
+      if constexpr (sizeof(IO) > sizeof(ST)) {
+        if (route.waves == 4) {
+          hipLaunchKernelGGL((read_partial_kernel<IO, ST, 4, kDirectLeaf, NT>), grid, dim3(256), 0, stream, p);
+          return;
+        }
+      }
       hipLaunchKernelGGL((read_partial_kernel<IO, ST, 8, kDirectLeaf, NT>), grid, dim3(512), 0, stream, p);
-    else if (route.waves == 4)
-      hipLaunchKernelGGL((read_partial_kernel<IO, ST, 4, 32, NT>), grid, dim3(256), 0, stream, p);
-    else
-      hipLaunchKernelGGL((read_partial_kernel<IO, ST, 8, 32, NT>), grid, dim3(512), 0, stream, p);
+    } else if constexpr (sizeof(IO) <= sizeof(ST)) {
+      if (route.waves == 4)
+        hipLaunchKernelGGL((read_partial_kernel<IO, ST, 4, 32, NT>), grid, dim3(256), 0, stream, p);
+      else
+        hipLaunchKernelGGL((read_partial_kernel<IO, ST, 8, 32, NT>), grid, dim3(512), 0, stream, p);
+    }
   };
   if (route.nt) run(std::true_type{});
   else run(std::false_type{});

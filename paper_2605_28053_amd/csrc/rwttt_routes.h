@@ -85,10 +85,23 @@ inline ReadRoute read_route(bool io_bf16, bool state_bf16, int d_ff, int d_model
              blocks <= (io_bf16 && !state_bf16 ? kDirectBlocksTwo : kDirectBlocks);
   r.nt = !stays_cached(bytes, context_bytes);
   // leaves of eight rows where the one launch above must match, and for fp32 io
-  // with bf16 state, where they are faster (20.0 against 23.4 us for two owners
-  // of 3600 x 1512)
+  // with bf16 state, where they are faster (14.5 against 21.4 us for one owner of
+  // 3600 x 1512, 115.6 / 125.6 for eight of 9728 x 2560)
   r.leaf = d_ff <= kDirectRows || io > state ? 8 : 32;
-  r.waves = r.leaf == 32 && count == 1 ? 4 : 8;
+  if (r.leaf == 32) {
+    r.waves = count == 1 ? 4 : 8;
+    return r;
+  }
+  // fp32 io with bf16 state needs 138 registers: one block of eight waves fits a CU,
+  // or three of four waves, twelve waves.  Past one round of the 256 CUs the smaller
+  // blocks are better, unless much of the last column tile is empty.  Eight / four
+  // waves, in us: 14.5 / 14.8 at 3600 x 1512, 24.6 / 24.5 at 5000 x 1528 x 4 (239 blocks'
+  // worth of columns), 38.8 / 37.5 with five owners, 115.7 / 109.2 at 9728 x 2560 x 8,
+  // 260.5 / 239.7 at 14336 x 4096 x 8; 31.2 / 35.9 at 12000 x 520 x 4 and 48.0 / 51.2 with
+  // eight.  Four waves forced into 128 registers spill (149 us at 9728 x 2560 x 8).
+  const int ktile = read_tile_n(state_bf16), nt = (d_model + ktile - 1) / ktile;
+  const bool rounds = size_t(d_ff) * d_model * count > size_t(256) * kReadChunk * ktile;
+  r.waves = io > state && d_ff > kDirectRows && rounds && d_model * 4 > nt * ktile * 3 ? 4 : 8;
   return r;
 }
 

@@ -139,6 +139,7 @@ def test_f32_write_keeps_non_finite_evidence_in_its_place():
 READ_ROUTES = [
     (264, 4104, "bf16", "f32", 12), (1024, 2056, "bf16", "bf16", 9), (1032, 2056, "bf16", "f32", 5),
     (1536, 1032, "f32", "f32", 8), (1544, 1032, "bf16", "f32", 8), (3600, 520, "f32", "bf16", 3),
+    (3600, 1512, "f32", "bf16", 7),                          # four waves in a group, eight alone
     (8, 8, "f32", "f32", 2), (16, 72, "bf16", "f32", 3), (8, 8200, "bf16", "bf16", 8), (16, 8200, "bf16", "f32", 6),
 ]
 

@@ -88,6 +88,22 @@ def test_one_launch_read_needs_few_rows_bytes_and_blocks(ask):
         assert d == direct, call
 
 
+def test_waves_of_a_read_block(ask):
+    """Four waves: one owner, and fp32 io with bf16 state past one round of blocks
+    whose last column tile is not mostly empty."""
+    def waves(*call):
+        (direct, w, *_), = ask("read " + " ".join(map(str, call)) + f" {BIG}")
+        assert direct == "0"
+        return w
+    for call in ((9728, 2560, 2), (9728, 2560, 8), (5000, 1528, 5), (3600, 1512, 7), (12000, 1000, 8)):
+        assert waves("f32", "bf16", *call) == "4", call
+    for call in ((3600, 1512, 1), (5000, 1528, 4), (2048, 2048, 8), (12000, 520, 8), (1536, 4096, 16)):
+        assert waves("f32", "bf16", *call) == "8", call
+    for io, state in (("bf16", "f32"), ("bf16", "bf16"), ("f32", "f32")):
+        assert waves(io, state, 9728, 2560, 1) == "4"
+        assert waves(io, state, 9728, 2560, 2) == waves(io, state, 9728, 2560, 8) == "8"
+
+
 def test_small_bf16_states_without_a_token_stream(ask):
     """bf16 state, C <= 64: the streaming kernel up to one item a CU (both sides
     of the line), and one owner whose blocks fill its slots."""
