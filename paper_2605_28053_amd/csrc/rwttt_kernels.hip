@@ -1327,7 +1327,9 @@ hipError_t launch_read_t(const ReadLaunch& L, hipStream_t stream, float* slot_pa
   auto run = [&](auto nt) {
     constexpr bool NT = decltype(nt)::value;
     if (route.leaf == kDirectLeaf) {
-      if constexpr (sizeof(IO) > sizeof(ST)) {
+      // so large a call always has the hint
+      static_assert(size_t(256) * kReadChunk * read_tile_n(1) * sizeof(ST) > kCacheCall, "");
+      if constexpr (sizeof(IO) > sizeof(ST) && NT) {
         if (route.waves == 4) {
           hipLaunchKernelGGL((read_partial_kernel<IO, ST, 4, kDirectLeaf, NT>), grid, dim3(256), 0, stream, p);
           return;
