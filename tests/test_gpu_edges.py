@@ -1,13 +1,18 @@
 """Kernels at the sizes where their tiles, waves and dispatch rules change,
 against the oracle in float64, through the C ABI.
 
-fp32 results are judged by the norm of the error over the norm of the result:
-every fp32 kernel adds each product in a chain of at most 32 roundings of a
-running sum plus trees, and such sums of independent terms err by about
-sqrt(32) 2^-25 = 1.7e-7 in the norm per stage, so 1e-6 leaves a factor of
-three over two stages.  bf16 results add one rounding, 2^-9 at most per value
-(1.7e-3 in the norm; 4e-3 bound).
+fp32 results are judged by the norm of the error over the norm of the result.
+A running sum of n independent terms errs by about sqrt(n / 6) 2^-24 in the norm
+when each rounding is uniform over half an ulp of a partial sum that grows as a
+square root: 2.0e-7 for the 64 products of a READ leaf (32 rows of dW and W0), 7.8e-7
+for the longest chain here, the 1024 evidence rows of an fp32 WRITE (one accumulator
+over the whole chunk; 1.5e-7 for 40 rows).  The adapter kernels' chains have at most
+16 products, and trees and short second stages add less, so 1e-6 holds for all.
+bf16 results add one rounding, 2^-9 at most per value (1.7e-3 in the norm; 4e-3
+bound).
 """
+
+import dataclasses
 
 import numpy as np
 import pytest
@@ -89,7 +94,7 @@ def test_adapter_write_keeps_non_finite_evidence_in_its_place():
 F32_WRITES = [
     (4096, 264, "f32", 2), (4104, 136, "f32", 3), (8200, 72, "f32", 6),
     (8, 8, "f32", 1), (256, 64, "f32", 4), (264, 72, "bf16", 5), (248, 56, "f32", 15), (512, 136, "bf16", 16),
-    (776, 200, "f32", 17), (1032, 1032, "f32", 130),
+    (776, 200, "f32", 17), (1032, 1032, "f32", 130), (264, 72, "f32", 1024),
 ]
 
 
@@ -172,13 +177,13 @@ def test_read_routes_agree_bit_for_bit(d_ff, d_model, io, state, n):
 # bf16 evidence without a token.  fp32 state, register operands: the smallest
 # matrix, a tile of 64 x 64 and its remainders (8 rows in a lane's second run,
 # one column group past the tile), a count of tiles no block of four divides;
-# chunk: one, a group of 16 and past it, the last of this path and the first of
-# the GEMM.  bf16 state: streaming and GEMM on both sides of the small-state line
+# chunk: one, a group of 16 and past it, the last of this path and the first three
+# counts of GEMM stages past it (13 to 15: the last stage in each of its three buffers).  bf16 state: streaming and GEMM on both sides of the small-state line
 # (2.2 M elements of a group, one item a block), chunks of one and two GEMM stages
 # of 32 ranks; a row of GEMM tiles and a column of them, fewer than the XCDs
 ROWS_WRITES = [
     (8, 8, "f32", 1), (64, 64, "f32", 16), (72, 72, "f32", 17), (136, 328, "f32", 33), (248, 1032, "f32", 64),
-    (520, 264, "f32", 384), (520, 264, "f32", 385), (8, 8, "bf16", 1), (264, 136, "bf16", 31), (520, 136, "bf16", 33),
+    (520, 264, "f32", 384), (520, 264, "f32", 385), (264, 136, "f32", 417), (264, 264, "f32", 449), (8, 8, "bf16", 1), (264, 136, "bf16", 31), (520, 136, "bf16", 33),
     (264, 264, "bf16", 64), (2048, 512, "bf16", 17), (2056, 512, "bf16", 64), (1544, 1032, "bf16", 33),
     (72, 16392, "bf16", 64), (8200, 72, "bf16", 20), (264, 4104, "bf16", 70),
 ]
@@ -255,3 +260,116 @@ def test_bf16_write_with_token_edges(d_ff, d_model, chunk):
         torch.cuda.synchronize()
         assert torch.equal(alone[r], y[r]) and torch.equal(sess.shadow(r, 0), both[i])
     assert torch.isnan(y[1]).all()
+
+
+# Every kernel that loads the live state with and without the non-temporal hint:
+# a context of few owners, and one whose states do not fit the 256 MB cache.  An
+# owner must also have the same bits alone and in a group, on both sides of the
+# rules that look at the group.
+BOTH_HINTS = [
+    # d_ff, d_model, io, state, chunk (0: READ), token, group, owners of the large context
+    (2056, 1032, "bf16", "f32", 0, False, 2, 32),     # READ: eight waves, four alone
+    (2056, 1032, "bf16", "bf16", 0, False, 3, 64),
+    (1024, 2056, "bf16", "f32", 0, False, 5, 32),     # two launches, one alone
+    (2056, 1032, "f32", "bf16", 0, False, 3, 64),
+    (2000, 776, "bf16", "f32", 33, True, 3, 44),      # register operands with token
+    (4104, 512, "bf16", "f32", 64, True, 3, 32),      # streaming with token
+    (2056, 1032, "bf16", "bf16", 17, True, 3, 64),
+    (2000, 776, "bf16", "f32", 100, False, 3, 44),    # register operands
+    (520, 264, "bf16", "f32", 400, True, 2, 500),     # READ, then the GEMM with fp32 state
+    (1544, 1032, "bf16", "bf16", 33, False, 3, 84),   # GEMM, streaming alone
+    (4096, 264, "f32", "f32", 5, True, 3, 64),        # fp32 evidence: blocks of 64 rows
+    (4104, 520, "f32", "f32", 40, True, 3, 32),       # ... of 128
+    (8200, 264, "f32", "bf16", 17, True, 3, 64),      # ... of 256
+    (4104, 520, "f32", "f32", 40, False, 3, 32),
+]
+
+
+@pytest.mark.parametrize("d_ff,d_model,io,state,chunk,token,n,many", BOTH_HINTS)
+def test_same_bits_with_either_cache_hint_and_in_any_group(d_ff, d_model, io, state, chunk, token, n, many):
+    say("cache hint", d_ff, d_model, io, state, chunk, token)
+    wl = small_workload(d_ff, d_model, io, state, n)
+    src = TensorSource(wl)
+    small = Session(wl, src)
+    large = Session(dataclasses.replace(wl, n_owners=many), None, max_group=n)
+    large.w0[0].copy_(small.w0[0])
+    for r in range(n):
+        large.slots[r][0][0].copy_(small.slots[r][0][0])
+    x = draw((many, d_ff), 1.0, io, wl.seed, (65, chunk))
+    xd = to_device(x, io)
+    ev = [evidence(wl, chunk, r) for r in range(n)] if chunk else []
+    dev = [(to_device(z, io), to_device(g, io)) for z, g in ev]
+
+    def call(sess, owners):
+        """{owner: (token or y, candidate)}"""
+        y = torch.full((many, d_model), 7.0, device="cuda", dtype=xd.dtype)
+        if not chunk:
+            read_group(sess, owners, 0, xd, y)
+        else:
+            assert write_group(sess, owners, 0, chunk, [dev[r][0] for r in owners], [dev[r][1] for r in owners], None,
+                               *((xd, y) if token else ())) == R.RWTTT_OK
+            assert R.rwttt_rollback(sess.ctx, owners) == R.RWTTT_OK
+        torch.cuda.synchronize()
+        assert torch.all(y[n:] == 7.0)
+        return {r: (y[r].clone(), sess.shadow(r, 0).clone() if chunk else y[r]) for r in owners}
+
+    group = list(range(n))[::-1]
+    want = call(small, group)
+    runs = [call(large, group)] + [call(sess, [r]) for sess in (small, large) for r in group]
+    for run in runs:
+        for r, (y, cand) in run.items():
+            assert torch.equal(y, want[r][0]) and torch.equal(cand, want[r][1]), r
+    live = O.widen(src.dw_init(0, 0), state)
+    if token or not chunk:
+        ref = O.read_apply(O.widen(x[0], io), O.widen(src.w0(0), io), live)
+        assert rel_norm(host_f64(want[0][0], io), ref) <= norm_tol(io)
+    if chunk:
+        ref = O.write_candidate(live, O.widen(ev[0][0], io), O.widen(ev[0][1], io), wl.eta)
+        assert rel_norm(host_f64(want[0][1], state), ref) <= norm_tol(state)
+
+
+# One WRITE path each: register operands with a token and without, streaming, fp32
+# evidence with 64 and 256 rows per token partial, READ then the GEMM
+TWO_STREAMS = [
+    (2000, 776, "bf16", "f32", 33, True), (2000, 776, "bf16", "f32", 100, False), (4104, 512, "bf16", "f32", 64, True),
+    (4096, 264, "f32", "f32", 5, True), (8200, 264, "f32", "f32", 17, True), (1000, 264, "bf16", "bf16", 70, True),
+]
+
+
+@pytest.mark.parametrize("d_ff,d_model,io,state,chunk,token", TWO_STREAMS)
+def test_writes_and_reads_of_disjoint_owners_on_two_streams(d_ff, d_model, io, state, chunk, token):
+    """Two WRITEs, then a WRITE beside a READ, overlapping on two streams with
+    disjoint owners: the bits of the same calls one after the other."""
+    say("two streams", d_ff, d_model, io, state, chunk, token)
+    wl = small_workload(d_ff, d_model, io, state, 5)
+    src = TensorSource(wl)
+    sess = Session(wl, src)
+    xd = to_device(draw((5, d_ff), 1.0, io, wl.seed, (66,)), io)
+    dev = {r: [to_device(t, io) for t in evidence(wl, chunk, r)] for r in range(5)}
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+
+    def write(owners, y):
+        assert write_group(sess, owners, 0, chunk, [dev[r][0] for r in owners], [dev[r][1] for r in owners], None,
+                           *((xd, y) if token else ())) == R.RWTTT_OK
+
+    def read(owners, y):
+        read_group(sess, owners, 0, xd, y)
+
+    for first, second in ((write, write), (write, read)):
+        results = []
+        for overlap in (False, True, True, True):
+            y = [torch.zeros((5, d_model), device="cuda", dtype=xd.dtype) for _ in range(2)]
+            for r in range(5):
+                sess.shadow(r, 0).zero_()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(streams[0]):
+                first([3, 0], y[0])
+            if not overlap:
+                torch.cuda.synchronize()
+            with torch.cuda.stream(streams[1]):
+                second([1, 4, 2], y[1])
+            torch.cuda.synchronize()
+            assert R.rwttt_rollback(sess.ctx, [3, 0] + ([1, 4, 2] if second is write else [])) == R.RWTTT_OK
+            results.append(y + [sess.shadow(r, 0).clone() for r in range(5)])
+        for got in results[1:]:
+            assert all(torch.equal(a, b) for a, b in zip(got, results[0]))

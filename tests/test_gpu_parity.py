@@ -124,7 +124,8 @@ WRITE_CASES = [
     (9728, 2560, "bf16", "f32", 64, [1]),
     (264, 136, "bf16", "f32", 33, [11, 4, 0, 7, 2, 9, 5, 1, 10, 3, 8, 6]),   # 12 owners, stream path
     (264, 136, "bf16", "bf16", 130, [9, 2, 5, 0, 7, 3, 8, 1, 6, 4]),        # 10 owners, GEMM path
-    (264, 520, "f32", "bf16", 5, [1, 0]),              # fp32 evidence into bf16 state (VALU path)
+    (264, 520, "f32", "bf16", 5, [1, 0]),              # fp32 evidence into bf16 state
+    (264, 264, "bf16", "f32", 390, [1, 0]),            # GEMM with fp32 state
     (2056, 264, "bf16", "bf16", 64, [2, 0]),           # 65 row tiles over 33 partitions of 2 and 1 items
     (3080, 264, "bf16", "f32", 48, [0, 2, 1]),         # 97 row tiles over 49 partitions of 2 and 1 items
 ]
@@ -188,8 +189,10 @@ TOKEN_CASES = [
     (1576, 520, "bf16", "f32", 64, [4, 0, 2], 5),     # 50 row tiles, one per partition
     (2056, 264, "bf16", "bf16", 64, [2, 0, 3], 4),    # bf16 state, partitions of 2 and 1 items
     (3080, 264, "bf16", "f32", 48, [1, 0], 3),        # fp32 state, partitions of 2 and 1 items
-    (264, 520, "f32", "bf16", 5, [1, 0], 2),          # fp32 evidence, bf16 state: READ, then VALU
-    (520, 1032, "bf16", "f32", 100, [3, 0], 4),       # large chunk: READ, then the GEMM
+    (264, 520, "f32", "bf16", 5, [1, 0], 2),          # fp32 evidence, bf16 state
+    (520, 1032, "bf16", "f32", 100, [3, 0], 4),       # large chunk: READ, then register operands
+    (520, 264, "bf16", "f32", 400, [3, 0], 4),        # larger: READ, then the GEMM
+    (520, 264, "bf16", "bf16", 100, [1, 2], 4),       # bf16 state: READ, then the GEMM
     (256, 64, "f32", "f32", 4, [0, 1], 2),            # fp32 evidence
     (9728, 2560, "bf16", "f32", 64, [5, 1, 7], 8),    # full 4B-layer shape
 ]
@@ -271,7 +274,7 @@ TAIL_CASES = [
     # io, state, chunk
     ("bf16", "f32", 4),
     ("bf16", "bf16", 17),
-    ("bf16", "f32", 70),      # large chunk: READ for the token, then the GEMM
+    ("bf16", "f32", 70),      # large chunk: READ for the token, then register operands
     ("f32", "f32", 4),        # fp32 evidence
 ]
 
@@ -557,12 +560,13 @@ def test_read_bf16_output_rounding_is_exact():
         assert np.array_equal(to_host(y[r], "bf16"), want), r
 
 
-@pytest.mark.parametrize("chunk", [1, 128, 150, 170])
-def test_write_bf16_state_rounding_is_exact(chunk):
+@pytest.mark.parametrize("chunk,token", [(1, False), (64, False), (1, True), (64, True), (128, False), (150, False),
+                                         (170, False)])
+def test_write_bf16_state_rounding_is_exact(chunk, token):
     """live + 1.0 * Z^T G with one unit rank is an exact fp32 sum; the bf16 shadow must be RNE.
 
-    chunk 1 takes the streaming WRITE kernel, the others the GEMM kernel, whose last rank stage
-    then sits in each of its three LDS stages in turn (4, 5 and 6 stages of 32 ranks).
+    Chunks up to 64 take the streaming WRITE kernel in its two forms, the others the GEMM kernel, whose
+    last rank stage then sits in each of its three LDS stages in turn (4, 5 and 6 stages of 32 ranks).
     """
     d_ff, d_model = 256, 512
     wl = small_workload(d_ff, d_model, "bf16", "bf16", 1, eta=1.0)
@@ -573,7 +577,10 @@ def test_write_bf16_state_rounding_is_exact(chunk):
     Z = np.zeros((chunk, d_ff), dtype=np.uint16)
     Z[chunk - 1, :] = 0x3F80                     # rank chunk-1 is all ones
     G = draw((chunk, d_model), 1.0, "bf16", 3, (2,))
-    st = write_group(sess, [0], 0, chunk, [to_device(Z, "bf16")], [to_device(G, "bf16")], eta=1.0)
+    x = torch.zeros((1, d_ff), dtype=torch.bfloat16, device="cuda")
+    y = torch.zeros((1, d_model), dtype=torch.bfloat16, device="cuda")
+    st = write_group(sess, [0], 0, chunk, [to_device(Z, "bf16")], [to_device(G, "bf16")], 1.0,
+                     *((x, y) if token else ()))
     assert st == R.RWTTT_OK
     torch.cuda.synchronize()
     want = O.bf16_bits(O.round_to(O.write_candidate(O.widen(L, "bf16"), O.widen(Z, "bf16"),
@@ -590,10 +597,12 @@ def test_write_bf16_state_rounding_is_exact(chunk):
 # --------------------------------------------------------------------------
 
 DEGENERATE_CASES = [
-    # d_ff, d_model, io, state, chunk: the streaming kernel, the GEMM, the fp32-evidence kernel
+    # d_ff, d_model, io, state, chunk: register operands, the streaming kernel, the GEMM with either
+    # state, register operands for a larger chunk, the fp32-evidence kernel
     (1000, 264, "bf16", "f32", 17),
     (1000, 264, "bf16", "bf16", 64),
     (520, 264, "bf16", "bf16", 150),
+    (520, 264, "bf16", "f32", 390),
     (520, 264, "bf16", "f32", 100),
     (256, 64, "f32", "f32", 4),
     (264, 520, "f32", "bf16", 5),
