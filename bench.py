@@ -43,7 +43,7 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-KERNEL_SOURCES = ("rwttt_kernels.hip", "rwttt_device.h", "rwttt_kernels.h")
+KERNEL_SOURCES = ("rwttt_kernels.hip", "rwttt_device.h", "rwttt_kernels.h", "rwttt_routes.h")
 
 
 def code_lines(text):
@@ -211,7 +211,8 @@ def write_kernel_name(wl, chunk, rank=0):
     if wl.io_dtype != "bf16":
         return "write_f32_kernel"
     if chunk <= 64:       # with its token, as every decode WRITE of the workloads
-        return "write_stream_kernel"
+        small = wl.d_ff <= 4096 and wl.d_model >= 512 and wl.d_ff * wl.d_model <= 4 << 20
+        return "write_rows_token_kernel" if wl.state_dtype == "f32" and small else "write_stream_kernel"
     return "write_rows_kernel" if wl.state_dtype == "f32" and chunk <= 384 else "write_gemm_kernel"
 
 

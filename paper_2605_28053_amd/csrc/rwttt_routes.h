@@ -161,7 +161,11 @@ constexpr int kRMaxC = 384;              // largest chunk without a fused token 
 // more rows, win with few owners (26.7 / 31.2 at 6000 x 600 x 3) and lose with many
 // (69.6 / 64.3 with eight, 106.0 / 91.8 at 8000 x 1000 x 6), and one wave wide
 // lose (137.5 / 118.7 at 14000 x 1400 x 3); bf16 state has half the bytes for the
-// same evidence loads (36.8 / 34.5 at 9728 x 2560).  The rule looks at the matrix
+// same evidence loads (36.8 / 34.5 at 9728 x 2560).  Inside it, rows that are no
+// whole 128-byte lines and columns padded by an eighth or more win with one owner
+// and lose with many: 10.9 / 12.3 at 2496 x 824 x 1, C = 40, but 43.6 / 39.9 with
+// eight owners; 12.8 / 13.6 and 66.0 / 62.4 at 4000 x 904; 11.1 / 12.7 and 48.6 / 46.5 at
+// 3000 x 776; 11.0 / 12.3 and 45.1 / 45.4 at 4096 x 520.  The rule looks at the matrix
 // alone: the two kernels add a token's rows in different orders.
 constexpr size_t kRTokenElems = size_t(4) << 20;
 
