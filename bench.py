@@ -485,7 +485,7 @@ def pmc_summary(dirs):
 
     def rows(d):
         (db,) = glob.glob(os.path.join(d, "*_results.db"))
-        q = ("select p.name, p.counter_value, k.grid_x, k.grid_y from pmc_events p "
+        q = ("select p.name, p.counter_value, k.grid_x / k.workgroup_x, k.grid_y from pmc_events p "
              "join kernels k on k.dispatch_id = p.dispatch_id")
         return sqlite3.connect(db).execute(q).fetchall()
 
@@ -508,7 +508,7 @@ def pmc_summary(dirs):
     for cn in per:
         for (name, gx, gy), vs in per[cn].items():
             if name == "read_partial_kernel":
-                e = table.setdefault(str(gx // 256 // pairs8), {"fetch": 0.0, "write": 0.0})
+                e = table.setdefault(str(gx // pairs8), {"fetch": 0.0, "write": 0.0})
                 e["fetch" if cn == "FETCH_SIZE" else "write"] += sum(vs) / len(vs)
     for cn in per:
         for (name, gx, gy), vs in per[cn].items():

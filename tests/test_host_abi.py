@@ -302,8 +302,8 @@ def test_bench_traffic_applies_only_to_its_shape_and_source(tmp_path, monkeypatc
 
 def test_bench_pmc_summary_scales_and_groups_by_call(tmp_path):
     """The PMC summariser scales each counter by the copy calibration and sums a
-    READ call's partial and reduce launches per group size (synthetic databases
-    with the rocpd columns it reads)."""
+    READ call's partial and reduce launches per group size, whatever the block
+    size (synthetic databases with the rocpd columns it reads)."""
     import sqlite3
     import bench
     ns = "void rwttt::(anonymous namespace)::"
@@ -316,16 +316,16 @@ def test_bench_pmc_summary_scales_and_groups_by_call(tmp_path):
         path.mkdir()
         c = sqlite3.connect(str(path / "x_results.db"))
         c.execute("create table pmc_events (dispatch_id int, name text, counter_value real)")
-        c.execute("create table kernels (dispatch_id int, grid_x int, grid_y int)")
+        c.execute("create table kernels (dispatch_id int, grid_x int, grid_y int, workgroup_x int)")
         for i, (name, v, gx, gy) in enumerate(rows):
             c.execute("insert into pmc_events values (?, ?, ?)", (i, name, v))
-            c.execute("insert into kernels values (?, ?, ?)", (i, gx, gy))
+            c.execute("insert into kernels values (?, ?, ?, ?)", (i, gx, gy, 512 if name == part else 256))
         c.commit()
 
     kib = (1 << 30) / 1024
     db(tmp_path / "pmc_copy_FETCH_SIZE", [(copy, kib / 2, 1, 1)])    # reads half: scale 2
     db(tmp_path / "pmc_copy_WRITE_SIZE", [(copy, kib, 1, 1)])
-    blocks8 = 384 * 8 * 256
+    blocks8 = 384 * 8 * 512
     db(tmp_path / "pmc_bench_FETCH_SIZE", [(part, 100.0, blocks8, 1), (part, 300.0, blocks8, 1),
                                            (red, 10.0, 10240, 8), (red, 1.0, 10240, 1),
                                            (wst, 50.0, 122880, 1)])
