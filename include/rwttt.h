@@ -126,9 +126,10 @@ typedef struct rwttt_config {
 /* Bytes of device workspace a context with this config needs: the READ
  * split-K partial sums, n_owners x ceil(d_ff/256) x d_model fp32 values
  * (d_model rounded up to the column tile), and the fused WRITE token's
- * partial sums, n_owners x 64 x d_model fp32 values (one per row-tile
- * partition of the streaming WRITE; the shape fixes at most 64 of them,
- * d_model rounded up to 256); for the adapter backend
+ * partial sums, n_owners x 64 x d_model fp32 values (one row for each group
+ * of matrix rows that a WRITE kernel sums by itself; the shape and the types
+ * fix at most 64 of them, and fp32 evidence of more than 8192 rows uses the
+ * READ region instead; d_model rounded up to 256); for the adapter backend
  * also n_owners x ceil(d_ff/256) x r partial sums of x A and two
  * n_owners x RWTTT_ADAPTER_MAX_CHUNK x r scratch matrices of a WRITE; one
  * region per owner.  Only the shape fields are read.  The workspace needs no
@@ -184,10 +185,11 @@ rwttt_status rwttt_plan(const rwttt_ctx* ctx, const rwttt_event* ev, uint32_t n_
  * are bit-identical whatever the group's size, order or other members.
  * An empty group returns RWTTT_OK and launches nothing.  Launches two kernels
  * on `stream` (split-K partial sums into the owners' workspace regions, then
- * their reduction), or one for few rows (d_ff <= 1536) and little state.  Reads and writes of one context may run concurrently on
- * different streams when they name disjoint owners (the serving contract
- * gives each owner one transition per step); calls that share an owner must
- * be ordered on the device (same stream, or an event wait).
+ * their reduction), or one for few rows (d_ff <= 1536) and little state.  Reads
+ * and writes of one context may run concurrently on different streams when
+ * they name disjoint owners (the serving contract gives each owner one
+ * transition per step); calls that share an owner must be ordered on the
+ * device (same stream, or an event wait).
  *
  * expected: NULL, or a host array indexed like owner_map (entry first+b
  * belongs to slot b) holding the version each member was planned at

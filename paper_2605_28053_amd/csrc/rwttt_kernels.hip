@@ -44,7 +44,8 @@ namespace {
 //    where the chain of rounds is all there is.  More in flight (16 rows at a
 //    time, or 16 waves) is slower: 142-147 us for the first.  One owner alone
 //    keeps the four-wave block, 64 rows as two leaves of 32, so that the bits
-//    are the same: 27.5 against 27.8 us at 9728 x 2560.
+//    are the same: 27.5 against 27.8 us at 9728 x 2560.  So do large calls of bf16
+//    state with fp32 io, as eight leaves of 8.
 // 2. read_reduce_kernel: y[b, n] = sum over chunks: four contiguous quarters
 //    of the chunks, each in chunk order, added in order (as a tree for few
 //    rows).
