@@ -139,11 +139,18 @@ inline int stream_parts(int d_ff, int d_model) {
 //   evidence: 21.2 / 22.2 at 9728 x 2560, 43.4 / 45.1 at 14336 x 4096, C = 16 (the
 //   latter 46.4 / 46.0 at C = 48); rows that are no whole 128-byte lines cost the
 //   GEMM's narrower tiles more, at every C: 21.0 / 23.8 at 10000 x 2000.
+// * few rows leave most of the GEMM's 256 empty.  Up to 32 always: 7.6 / 12.3 at 32 x
+//   14336 x 8, C = 1, 27.5 / 41.6 with 32 owners, C = 64, 16.8 / 36.5 at 8 x 14336 x 32.  Up
+//   to 64 a limit: 7.8 / 8.4 at 64 x 14336 x 4, C = 64, 13.9 / 14.2 with eight owners, 27.4 /
+//   24.7 with 16.  At 72 rows 12.4 / 8.7 at 72 x 14336 x 4.
 constexpr size_t kSSmallElems = 2200000;   // 256 blocks of one 32 x 256 item
+constexpr size_t kSFewRowsElems = 8000000;
 
 inline bool stream_without_token(int d_ff, int d_model, int count, int chunk, size_t context_bytes) {
   const int parts = stream_parts(d_ff, d_model);
-  if (parts * kSTM >= d_ff && size_t(d_ff) * d_model * count <= kSSmallElems) return true;
+  const size_t elems = size_t(d_ff) * d_model * count;
+  if (d_ff <= kSTM || (d_ff <= 2 * kSTM && elems <= kSFewRowsElems)) return true;
+  if (parts * kSTM >= d_ff && elems <= kSSmallElems) return true;
   const int blocks = (d_model + kSTN - 1) / kSTN * parts;
   return count == 1 && blocks > kSSlots * 15 / 16 && blocks <= kSSlots && 
          ((context_bytes > kCacheContext && chunk <= 16) || d_model % 64 != 0);

@@ -278,6 +278,7 @@ BOTH_HINTS = [
     (2000, 776, "bf16", "f32", 100, False, 3, 44),    # register operands
     (520, 264, "bf16", "f32", 400, True, 2, 500),     # READ, then the GEMM with fp32 state
     (1544, 1032, "bf16", "bf16", 33, False, 3, 84),   # GEMM, streaming alone
+    (64, 16392, "bf16", "bf16", 33, False, 8, 130),   # ... few rows
     (4096, 264, "f32", "f32", 5, True, 3, 64),        # fp32 evidence: blocks of 64 rows
     (4104, 520, "f32", "f32", 40, True, 3, 32),       # ... of 128
     (8200, 264, "f32", "bf16", 17, True, 3, 64),      # ... of 256

@@ -105,15 +105,18 @@ def test_waves_of_a_read_block(ask):
 
 
 def test_small_bf16_states_without_a_token_stream(ask):
-    """bf16 state, C <= 64: the streaming kernel up to one item a CU (both sides
-    of the line), and one owner whose blocks fill its slots."""
+    """bf16 state, C <= 64: the streaming kernel up to one item a CU and for few
+    rows (both sides of the lines), and one owner whose blocks fill its slots."""
     def kernel(d_ff, d_model, count, chunk):
         (k, *_), = ask(f"write bf16 bf16 {d_ff} {d_model} {count} {chunk} 0 {BIG}")
         return k
     for small in ((8, 8, 1), (264, 136, 8), (1000, 264, 8), (1024, 1024, 2), (2048, 512, 2), (256, 4096, 2)):
         assert kernel(*small, 1) == kernel(*small, 64) == "stream", small
         assert kernel(*small, 65) == "gemm", small
-    for large in ((512, 2048, 4), (1024, 1024, 4), (2048, 512, 4), (5000, 128, 1), (8192, 64, 1), (9728, 2560, 2)):
+    for few_rows in ((8, 14336, 32), (32, 14336, 32), (64, 14336, 8), (40, 4096, 32)):
+        assert kernel(*few_rows, 1) == kernel(*few_rows, 64) == "stream", few_rows
+        assert kernel(*few_rows, 65) == "gemm", few_rows
+    for large in ((64, 14336, 16), (72, 14336, 4), (512, 2048, 4), (1024, 1024, 4), (2048, 512, 4), (5000, 128, 1), (8192, 64, 1), (9728, 2560, 2)):
         assert kernel(*large, 1) == kernel(*large, 64) == "gemm", large
     assert kernel(9728, 2560, 1, 16) == kernel(14336, 4096, 1, 16) == "stream"
     assert kernel(9728, 2560, 1, 48) == kernel(14336, 4096, 1, 48) == "gemm"
