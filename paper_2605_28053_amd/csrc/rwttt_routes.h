@@ -152,12 +152,13 @@ inline bool stream_without_token(int d_ff, int d_model, int count, int chunk, si
   if (d_ff <= kSTM || (d_ff <= 2 * kSTM && elems <= kSFewRowsElems)) return true;
   if (parts * kSTM >= d_ff && elems <= kSSmallElems) return true;
   const int blocks = (d_model + kSTN - 1) / kSTN * parts;
-  return count == 1 && blocks > kSSlots * 15 / 16 && blocks <= kSSlots && 
+  return count == 1 && blocks > kSSlots * 15 / 16 && blocks <= kSSlots &&
          ((context_bytes > kCacheContext && chunk <= 16) || d_model % 64 != 0);
 }
 
 constexpr int kRTM = 64;                 // register-operand kernels: rows per wave
 constexpr int kRMaxC = 384;              // largest chunk without a fused token on this path
+constexpr int kRMinC = 256;              // up to here always on this path, but for one full GEMM round
 
 // With a fused token: against the streaming kernel, whose blocks start with a
 // G tile staged through LDS and have few items on a small state, in us: 1000 x
@@ -223,6 +224,34 @@ constexpr unsigned gemm_blocks(int count, int mt, int ntl) {
   return unsigned(count) * mtq * ntg * 8u;
 }
 
+constexpr int kGSlots = 64;               // GEMM blocks resident at once on an XCD (32 CUs x 2)
+
+// Largest chunk of an fp32 state without a fused token for the register-operand
+// kernel, whose time grows by about 3 us for 1000 ranks of a million elements; the
+// GEMM's grows half as fast from a higher start, which is the higher the less its
+// tiles fill the rounds of its block slots (the XCD with most tiles counts).
+// Register operands / GEMM, in us:
+// * filled to 0.95 and more: 80.5 / 77.0 at 2000 x 2000 x 8, C = 320, 89.0 / 79.4 at C = 384
+//   (72.3 / 73.1 at 256); 104 / 99 and 114 / 103 at 4096 x 4096 x 3 (93 / 95), 263 / 248 and 291 /
+//   258 with eight owners (237 / 239);
+// * to 0.91: 171 / 158 at 5000 x 1528 x 8, C = 384, 398 / 423 at 9728 x 2560 x 8, C = 320,
+//   441 / 442 at 384;
+// * less: 153 / 171 at 9728 x 2560 x 3, C = 320, 169 / 177 at 384; 33.0 / 37.6 at 2000 x 2000 x
+//   3, 54.0 / 61.8 at 2496 x 824 x 8, C = 384;
+// * one round, filled: 36.2 / 33.3 at 4096 x 4096 x 1, C = 192, 48.2 / 37.8 at 384.
+// Both kernels add in the same order, so the group may be looked at.
+inline int rows_max_chunk(int d_ff, int d_model, int count) {
+  const int mt = (d_ff + kGTM - 1) / kGTM, ntl = (d_model + kGTN - 1) / kGTN;
+  if (gemm_few_tiles(mt, ntl)) return kRMaxC;
+  const int64_t most = int64_t(count) * ((mt + kGRowClasses - 1) / kGRowClasses) *
+                       ((ntl + kGColGroups - 1) / kGColGroups);
+  const int64_t rounds = (most + kGSlots - 1) / kGSlots;
+  const double fill = double(d_ff) * d_model * count / (double(rounds) * kGSlots * 8 * kGTM * kGTN);
+  if (rounds == 1 && fill >= 0.95) return 160;
+  // from kRMinC where the rounds are full to kRMaxC at nine tenths
+  return std::min(kRMaxC, kRMinC + int((kRMaxC - kRMinC) * 10 * (1 - fill)));
+}
+
 enum class WriteKernel { f32, rows_token, stream, rows, gemm };
 
 struct WriteRoute {
@@ -247,7 +276,7 @@ inline WriteRoute write_route(bool io_bf16, bool state_bf16, int d_ff, int d_mod
     return r;
   }
   r.read_first = token;
-  if (!state_bf16 && chunk <= kRMaxC) r.kernel = WriteKernel::rows;
+  if (!state_bf16 && chunk <= rows_max_chunk(d_ff, d_model, count)) r.kernel = WriteKernel::rows;
   if (state_bf16 && chunk <= kSMaxC && stream_without_token(d_ff, d_model, count, chunk, context_bytes)) {
     r.kernel = WriteKernel::stream;
     r.nt = true;             // also in a small context: 4.8 / 5.1 us with / without at 512 x 2048, C = 1
