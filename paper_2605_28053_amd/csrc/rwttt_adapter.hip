@@ -405,8 +405,9 @@ __global__ void __launch_bounds__(256) adapter_read_reduce_kernel(const AReadPar
 //    the eight waves contracts 128 elements for all 16 CT rows and all rank
 //    columns (JT tiles of 16); a lane's 16 bytes of evidence feed eight (bf16)
 //    matrix steps.  The waves' sums are added as a tree.  The factor slice is
-//    read once per evidence tile: CT = 4 halves that L2 traffic where rank <= 16
-//    leaves the registers for it and C > 128 the blocks.
+//    read once per evidence tile: CT = 4 halves that L2 traffic against 2 where
+//    rank <= 16 leaves the registers for it and C > 128 the blocks; CT = 1 where
+//    its blocks all fit the CUs at once.
 // 2. adapter_update_kernel: one block of NW waves per 64 rows k of A or columns
 //    n of B, all rank columns: A'[k][j] = A[k][j] + eta sum_c Z[c][k] P[c][j] and
 //    B'[j][n] = B[j][n] + eta sum_c Q[c][j] G[c][n].  The waves take contiguous
@@ -747,9 +748,11 @@ hipError_t launch_adapter_write_t(const AdapterWriteLaunch& L, hipStream_t strea
   using two = std::integral_constant<int, 2>;
   using four = std::integral_constant<int, 4>;
   using eight = std::integral_constant<int, 8>;
-  if (L.rank > 16) pq(two{}, two{});
-  else if (L.chunk <= 128) pq(one{}, two{});
-  else pq(one{}, four{});
+  switch (adapter_pq_tiles(int(slices), L.chunk, L.count, L.rank)) {
+    case 1: L.rank > 16 ? pq(two{}, one{}) : pq(one{}, one{}); break;
+    case 2: L.rank > 16 ? pq(two{}, two{}) : pq(one{}, two{}); break;
+    default: pq(one{}, four{});
+  }
   auto by_waves = [&](auto jt) {
     // a wave's group of loads is 16 evidence rows: eight waves have work for
     // each only above 64 (4.9 against 5.6 us at C = 64, one owner, rank 8)

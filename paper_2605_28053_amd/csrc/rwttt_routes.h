@@ -284,4 +284,21 @@ inline WriteRoute write_route(bool io_bf16, bool state_bf16, int d_ff, int d_mod
   return r;
 }
 
+// ---------------------------------------------------------------------------
+// Adapter WRITE
+// ---------------------------------------------------------------------------
+
+// Tiles of 16 evidence rows per block of the kernel that forms the products of
+// evidence and factors; slices: 1024-element slices of both extents.  A row's sums
+// do not depend on it.  One tile while its blocks fit the 256 CUs in one round:
+// larger ones only leave CUs idle.  In us, one tile / as below: 10.2 / 15.8 at 2000 x
+// 520 x 1, rank 1, C = 129 (27 blocks), 9.0 / 11.0 at 4608 x 304 x 1, C = 100, 11.4 / 13.8 at
+// 264 x 136 x 8, rank 20, C = 100, 13.8 / 16.8 at 4608 x 304 x 4 (168 blocks).  Past one
+// round 14.4 / 13.0 at 512 x 4096 x 8, rank 16, C = 100 (280 blocks), 16.6 / 15.1 at 14336 x
+// 4096 x 4, C = 64 (288), 24.9 / 24.2 at 9728 x 2560 x 4, C = 256 (832).
+inline int adapter_pq_tiles(int slices, int chunk, int count, int rank) {
+  if (int64_t(slices) * ((chunk + 15) / 16) * count <= 256) return 1;
+  return rank <= 16 && chunk > 128 ? 4 : 2;
+}
+
 }  // namespace rwttt

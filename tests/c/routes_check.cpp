@@ -1,6 +1,7 @@
 // Prints the dispatch rules' answers, one line for each query line of stdin:
 //   read io state d_ff d_model count context_bytes                -> direct waves leaf nt
 //   write io state d_ff d_model count chunk token context_bytes   -> kernel read_first wn nt
+//   adapter slices chunk count rank                               -> tiles of evidence rows per block
 //   gemm count mt ntl                                             -> 1 if every tile is dealt once, then tiles of each XCD
 #include <cstdio>
 #include <iostream>
@@ -38,6 +39,10 @@ int main() {
       const WriteRoute r =
           write_route(io == "bf16", state == "bf16", d_ff, d_model, count, chunk, token != 0, context);
       std::printf("%s %d %d %d\n", name(r.kernel), r.read_first, r.wn, r.nt);
+    } else if (what == "adapter") {
+      int slices, chunk, count, rank;
+      std::cin >> slices >> chunk >> count >> rank;
+      std::printf("%d\n", adapter_pq_tiles(slices, chunk, count, rank));
     } else if (what == "gemm") {
       int count, mt, ntl;
       std::cin >> count >> mt >> ntl;

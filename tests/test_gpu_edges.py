@@ -71,6 +71,28 @@ def test_adapter_write_edges(d_ff, d_model, io, state, rank, chunk):
             assert rel_norm(g, want) <= norm_tol(state), r
 
 
+# One tile of evidence rows a block for an owner alone; two and four, past one
+# round of blocks, for the group
+@pytest.mark.parametrize("d_ff,d_model,io,state,rank,chunk", [
+    (1032, 2056, "bf16", "f32", 16, 100), (1032, 2056, "f32", "f32", 5, 145), (1032, 2056, "bf16", "bf16", 17, 100)])
+def test_adapter_write_alone_has_the_groups_bits(d_ff, d_model, io, state, rank, chunk):
+    wl = small_workload(d_ff, d_model, io, state, 9)
+    say("adapter write alone and in a group", d_ff, d_model, io, state, rank, chunk)
+    sess = Session(wl, TensorSource(wl), backend=ADA, rank=rank)
+    group = list(range(9))[::-1]
+    dev = {r: [to_device(t, io) for t in evidence(wl, chunk, r)] for r in group}
+    assert write_group(sess, group, 0, chunk, [dev[r][0] for r in group], [dev[r][1] for r in group]) == R.RWTTT_OK
+    assert R.rwttt_rollback(sess.ctx, group) == R.RWTTT_OK
+    torch.cuda.synchronize()
+    want = {r: sess.shadow(r, 0).clone() for r in group}
+    for r in group:
+        sess.shadow(r, 0).zero_()
+        assert write_group(sess, [r], 0, chunk, [dev[r][0]], [dev[r][1]]) == R.RWTTT_OK
+        assert R.rwttt_rollback(sess.ctx, [r]) == R.RWTTT_OK
+        torch.cuda.synchronize()
+        assert torch.equal(sess.shadow(r, 0), want[r]), r
+
+
 def test_adapter_write_keeps_non_finite_evidence_in_its_place():
     """An infinite evidence value reaches what it enters and nothing else (rows
     past the chunk and columns past the rank are clamped copies of real ones)."""

@@ -138,6 +138,16 @@ def test_long_chunks_of_fp32_states_by_how_full_the_gemm_runs(ask):
         assert kernel(*call, rows) == "rows" and kernel(*call, gemm) == "gemm", call
 
 
+def test_adapter_write_tiles(ask):
+    """One tile of 16 evidence rows a block while the blocks fit 256 CUs, whatever
+    the chunk and rank; both sides of the line."""
+    for call, tiles in (((3, 129, 1, 1), "1"), ((2, 1024, 2, 16), "1"), ((13, 256, 1, 20), "1"), ((2, 128, 16, 32), "1"),
+                        ((2, 128, 17, 16), "2"), ((2, 129, 17, 16), "4"), ((2, 129, 17, 17), "2"), ((13, 256, 4, 16), "4"),
+                        ((2, 1040, 2, 16), "4"), ((2048, 1024, 64, 32), "2")):
+        (got,), = ask("adapter " + " ".join(map(str, call)))
+        assert got == tiles, call
+
+
 def test_the_cache_hint_follows_the_call_and_its_context(ask):
     """The hint is dropped where the context's live states and W0s fit the
     last-level cache and the call is small beside it; never where only one of the
