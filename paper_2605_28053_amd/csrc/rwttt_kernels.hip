@@ -1068,7 +1068,7 @@ write_f32_kernel(const WriteParams p) {
 // kernel (C <= 64) and the GEMM that took these calls before: 104 / 117 at C =
 // 64, 114 / 155 at 128, 137 / 165 at 256, 168 / 177 at 384.  The evidence loads
 // bind then (200 / 188 at 512), so longer chunks stay with the GEMM, and from C =
-// 256 on those of calls whose tiles fill its rounds.  One
+// 300 on those of calls whose tiles fill its rounds.  One
 // owner of 2496 x 824, C = 159: 8.7 / 15.4.  Half as many state rows per wave
 // needs nearly twice the loads per product (108, 125, 167 at 64, 128, 256).
 // With bf16 state, half the bytes, the GEMM is as fast at C = 16 (78 / 80 us

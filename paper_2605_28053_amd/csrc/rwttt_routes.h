@@ -158,7 +158,7 @@ inline bool stream_without_token(int d_ff, int d_model, int count, int chunk, si
 
 constexpr int kRTM = 64;                 // register-operand kernels: rows per wave
 constexpr int kRMaxC = 384;              // largest chunk without a fused token on this path
-constexpr int kRMinC = 256;              // up to here always on this path, but for one full GEMM round
+constexpr int kRMinC = 300;              // up to here always on this path, but for one full GEMM round
 
 // With a fused token: against the streaming kernel, whose blocks start with a
 // G tile staged through LDS and have few items on a small state, in us: 1000 x
@@ -231,14 +231,15 @@ constexpr int kGSlots = 64;               // GEMM blocks resident at once on an 
 // GEMM's grows half as fast from a higher start, which is the higher the less its
 // tiles fill the rounds of its block slots (the XCD with most tiles counts).
 // Register operands / GEMM, in us:
-// * filled to 0.95 and more: 80.5 / 77.0 at 2000 x 2000 x 8, C = 320, 89.0 / 79.4 at C = 384
-//   (72.3 / 73.1 at 256); 104 / 99 and 114 / 103 at 4096 x 4096 x 3 (93 / 95), 263 / 248 and 291 /
-//   258 with eight owners (237 / 239);
-// * to 0.91: 171 / 158 at 5000 x 1528 x 8, C = 384, 398 / 423 at 9728 x 2560 x 8, C = 320,
+// * filled to 0.95 and more, C = 300: 436 / 427 at 14336 x 4096 x 4, 72.7 / 66.6 at 8192 x
+//   4096 x 1, but 75.8 / 79.5 at 2048 x 2048 x 8 and 104 / 113 at 6144 x 2048 x 4; C = 384: 494 /
+//   443, 82.8 / 69.5, 84.8 / 83.3, 116 / 118, 291 / 258 at 4096 x 4096 x 8;
+// * to 0.91: 173 / 162 at 5000 x 1528 x 8, C = 384, 398 / 423 at 9728 x 2560 x 8, C = 320,
 //   441 / 442 at 384;
 // * less: 153 / 171 at 9728 x 2560 x 3, C = 320, 169 / 177 at 384; 33.0 / 37.6 at 2000 x 2000 x
-//   3, 54.0 / 61.8 at 2496 x 824 x 8, C = 384;
-// * one round, filled: 36.2 / 33.3 at 4096 x 4096 x 1, C = 192, 48.2 / 37.8 at 384.
+//   3, 54.0 / 61.8 at 2496 x 824 x 8, C = 384; the exception 136 / 120 at 14336 x 4096 x 1;
+// * one round, filled: 36.2 / 33.3 at 4096 x 4096 x 1, C = 192, 36.7 / 38.7 at 8192 x 2048 x 1,
+//   37.4 / 36.5 at 2048 x 1024 x 8, C = 200; 43.6 / 41.2 and 44.3 / 39.2 at C = 300.
 // Both kernels add in the same order, so the group may be looked at.
 inline int rows_max_chunk(int d_ff, int d_model, int count) {
   const int mt = (d_ff + kGTM - 1) / kGTM, ntl = (d_model + kGTN - 1) / kGTN;
@@ -247,7 +248,7 @@ inline int rows_max_chunk(int d_ff, int d_model, int count) {
                        ((ntl + kGColGroups - 1) / kGColGroups);
   const int64_t rounds = (most + kGSlots - 1) / kGSlots;
   const double fill = double(d_ff) * d_model * count / (double(rounds) * kGSlots * 8 * kGTM * kGTN);
-  if (rounds == 1 && fill >= 0.95) return 160;
+  if (rounds == 1 && fill >= 0.95) return 220;
   // from kRMinC where the rounds are full to kRMaxC at nine tenths
   return std::min(kRMaxC, kRMinC + int((kRMaxC - kRMinC) * 10 * (1 - fill)));
 }

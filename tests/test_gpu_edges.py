@@ -299,7 +299,7 @@ BOTH_HINTS = [
     (2056, 1032, "bf16", "bf16", 17, True, 3, 64),
     (2000, 776, "bf16", "f32", 100, False, 3, 44),    # register operands
     (520, 264, "bf16", "f32", 400, True, 2, 500),     # READ, then the GEMM with fp32 state
-    (2000, 2000, "bf16", "f32", 333, False, 8, 20),   # GEMM, register operands alone
+    (2000, 2000, "bf16", "f32", 345, False, 8, 20),   # GEMM, register operands alone
     (2048, 1016, "bf16", "f32", 300, True, 8, 40),    # ... after a READ
     (1544, 1032, "bf16", "bf16", 33, False, 3, 84),   # GEMM, streaming alone
     (64, 16392, "bf16", "bf16", 33, False, 8, 130),   # ... few rows
